@@ -18,6 +18,8 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # no packed FP32 instructions anywhere in the device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first twelve registers of kernel arguments are preloaded with a wave
+    "-mllvm", "-amdgpu-kernarg-preload-count=12",
     "-Wall", "-Wno-unused-function",
 ]
 

@@ -340,8 +340,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
         std::vector<unsigned char> host(lay.total, 0);
         c->corner.assign((size_t)n * 3, 0);
         TileRec *rec = reinterpret_cast<TileRec *>(host.data() + lay.rec_off);
-        uint64_t *nbm = reinterpret_cast<uint64_t *>(host.data() + lay.nbm_off);
-        uint32_t *nbb32 = reinterpret_cast<uint32_t *>(host.data() + lay.nbb32_off);
+        NbRow *row = reinterpret_cast<NbRow *>(host.data() + lay.row_off);
         uint64_t *nbb64 = reinterpret_cast<uint64_t *>(host.data() + lay.nbb64_off);
         int32_t *xyz = reinterpret_cast<int32_t *>(host.data() + lay.xyz_off);
         uint64_t *fbase = reinterpret_cast<uint64_t *>(host.data() + lay.fld_off);
@@ -369,10 +368,12 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
                 if (s < 0) continue;
                 const int32_t v = tiles->nbr[27 * i + k];
                 const TileRec r = v < 0 ? TileRec{0, 0} : rec[inv[v]];
-                nbm[NB_STRIDE * d + s] = r.mask;
-                nbb32[NB_STRIDE * d + s] = (uint32_t)r.base;
+                row[d].mask[s] = r.mask;
+                row[d].base32[s] = (uint32_t)r.base;
                 nbb64[NB_STRIDE * d + s] = r.base;
             }
+            row[d].fbase = fbase[d];
+            for (int a = 0; a < 3; ++a) row[d].xyz[a] = xyz[4 * d + a];
         }
         hipError_t e = hipMemcpyAsync(tables, host.data(), lay.total, hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -390,8 +391,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     c->L.tpw = c->params.tiles_per_wg;
     c->L.grid = (int)((n + c->L.tpw - 1) / c->L.tpw);
     c->L.tb.rec = reinterpret_cast<const TileRec *>(tb + lay.rec_off);
-    c->L.tb.nbm = reinterpret_cast<const uint64_t *>(tb + lay.nbm_off);
-    c->L.tb.nbb32 = reinterpret_cast<const uint32_t *>(tb + lay.nbb32_off);
+    c->L.tb.row = reinterpret_cast<const NbRow *>(tb + lay.row_off);
     c->L.tb.nbb64 = reinterpret_cast<const uint64_t *>(tb + lay.nbb64_off);
     c->L.tb.xyz = reinterpret_cast<const int32_t *>(tb + lay.xyz_off);
     c->L.tb.fbase = reinterpret_cast<const uint64_t *>(tb + lay.fld_off);

@@ -144,15 +144,19 @@ inline uint64_t run_elems(uint64_t mask, int storage) {
 // ---------------------------------------------------------------------------
 // device table layout inside the caller's `tables` buffer
 //   [rec_off]    TileRec per tile: fluid mask, element offset of its data
-//   [nbm_off]    uint64 [n_tiles][20]: fluid masks of the 19 tiles a D3Q19
-//                step reads from (the tile itself, 6 face and 12 edge
-//                neighbours; corners are never needed), 0 for a missing one
-//   [nbb32_off]  uint32 [n_tiles][20]: element offsets of the same 19 tiles
-//   [nbb64_off]  uint64 [n_tiles][20]: the same offsets in 64 bits
+//   [row_off]    NbRow per tile, 256 bytes on a 256-byte boundary: the fluid
+//                masks and 32-bit element offsets of the 19 tiles a D3Q19 step
+//                reads from (the tile itself, 6 face and 12 edge neighbours;
+//                corners are never needed; mask 0 for a missing tile), the
+//                entry offset of the tile's per-node field run and its corner
+//   [nbb64_off]  uint64 [n_tiles][20]: the 19 element offsets in 64 bits
 //   [xyz_off]    int32  [n_tiles][4]: corner x, y, z, 0
 //   [fld_off]    uint64 [n_tiles]: entry offset of the tile's per-node field run
 // The neighbourhood is gathered once on the host, so a wave reads it with a
-// few wide scalar loads instead of chasing 19 tile numbers.
+// few wide scalar loads instead of chasing 19 tile numbers.  Everything a step
+// needs to know about a tile is in its row: one round trip to memory, where a
+// record read before the row and a field offset read after it cost a wave two
+// more.
 // ---------------------------------------------------------------------------
 struct TileRec {
     uint64_t mask;
@@ -174,15 +178,23 @@ constexpr int nb_slot(int k) {
     }
     return -1;
 }
+struct alignas(64) NbRow {
+    uint64_t mask[19];
+    uint32_t base32[19];
+    uint32_t pad0;
+    uint64_t fbase;
+    int32_t xyz[3];
+    int32_t pad1;
+};
+static_assert(sizeof(NbRow) == 256, "a row is two whole 128-byte lines");
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct TableLayout {
-    size_t rec_off, nbm_off, nbb32_off, nbb64_off, xyz_off, fld_off, total;
+    size_t rec_off, row_off, nbb64_off, xyz_off, fld_off, total;
     explicit TableLayout(int64_t n_tiles) {
         const size_t n = (size_t)n_tiles;
         rec_off = 0;
-        nbm_off = align_up(rec_off + n * sizeof(TileRec), 256);
-        nbb32_off = align_up(nbm_off + n * NB_STRIDE * 8, 256);
-        nbb64_off = align_up(nbb32_off + n * NB_STRIDE * 4, 256);
+        row_off = align_up(rec_off + n * sizeof(TileRec), 256);
+        nbb64_off = align_up(row_off + n * sizeof(NbRow), 256);
         xyz_off = align_up(nbb64_off + n * NB_STRIDE * 8, 256);
         fld_off = align_up(xyz_off + n * 16, 256);
         total = align_up(fld_off + n * 8, 256);
@@ -191,8 +203,7 @@ struct TableLayout {
 
 struct DevTables {
     const TileRec *rec;
-    const uint64_t *nbm;
-    const uint32_t *nbb32;
+    const NbRow *row;
     const uint64_t *nbb64;
     const int32_t *xyz;
     const uint64_t *fbase;

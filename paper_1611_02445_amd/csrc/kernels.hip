@@ -133,19 +133,18 @@ __device__ __forceinline__ int remap_block_contiguous(int b, int nb) {
     return xcd * q + (xcd < r ? xcd : r) + local;
 }
 
-// wpb (waves per workgroup, a power of two up to 8) and nb (workgroups) come
+// lw (log2 of the waves per workgroup, at most 3) and nb (workgroups) come
 // in as kernel arguments: reading blockDim from the dispatch packet would cost
 // every wave a memory round trip before its first instruction of real work.
 constexpr int CHUNK_TILES_LOG2 = 5;
 template <bool CONTIGUOUS = false>
-__device__ __forceinline__ int wave_tile(int wpb, int nb) {
+__device__ __forceinline__ int wave_tile(int lw, int nb) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if constexpr (CONTIGUOUS) {
-        return remap_block_contiguous((int)blockIdx.x, nb) * wpb + wave;
+        return (remap_block_contiguous((int)blockIdx.x, nb) << lw) + wave;
     } else {
-        const int lw = __builtin_ctz((unsigned)wpb);  // workgroups per chunk = 32 / wpb
-        const int lc = lw < CHUNK_TILES_LOG2 ? CHUNK_TILES_LOG2 - lw : 0;
-        return remap_block((int)blockIdx.x, nb, lc) * wpb + wave;
+        const int lc = CHUNK_TILES_LOG2 - lw;  // workgroups per chunk = 32 >> lw
+        return (remap_block((int)blockIdx.x, nb, lc) << lw) + wave;
     }
 }
 
@@ -170,24 +169,40 @@ struct Nbhd {
     OffT base[27];   // element offset of each neighbour's data
 };
 
-template <typename OffT>
-__device__ __forceinline__ const OffT *nb_bases(const DevTables &tb);
-template <>
-__device__ __forceinline__ const uint32_t *nb_bases<uint32_t>(const DevTables &tb) { return tb.nbb32; }
-template <>
-__device__ __forceinline__ const uint64_t *nb_bases<uint64_t>(const DevTables &tb) { return tb.nbb64; }
+// A row as four 16-register scalar loads, waited for together: without the
+// empty asm the compiler waits for the tile's own mask alone, branches on it
+// and only then loads the rest of the row, a second round trip to memory
+// before the first gather can be issued.
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+struct RowRegs {
+    u32x16 q[4];
+    __device__ __forceinline__ explicit RowRegs(const NbRow *row, int t) {
+        const u32x16 *p = reinterpret_cast<const u32x16 *>(row + t);
+        q[0] = p[0];
+        q[1] = p[1];
+        q[2] = p[2];
+        q[3] = p[3];
+        asm volatile("" : "+s"(q[0]), "+s"(q[1]), "+s"(q[2]), "+s"(q[3]));
+    }
+    __device__ __forceinline__ uint32_t dword(int i) const { return q[i >> 4][i & 15]; }
+    __device__ __forceinline__ uint64_t qword(int i) const { return dword(i) | (uint64_t)dword(i + 1) << 32; }
+    __device__ __forceinline__ uint64_t mask(int s) const { return qword(2 * s); }
+    __device__ __forceinline__ uint32_t base32(int s) const { return dword((int)offsetof(NbRow, base32) / 4 + s); }
+    __device__ __forceinline__ uint64_t fbase() const { return qword((int)offsetof(NbRow, fbase) / 4); }
+    __device__ __forceinline__ uint32_t xyz(int c) const { return dword((int)offsetof(NbRow, xyz) / 4 + c); }
+};
 
 template <typename OffT>
-__device__ __forceinline__ void load_nbhd(Nbhd<OffT> &h, const DevTables &tb, int t) {
-    const uint64_t *m = tb.nbm + (size_t)t * NB_STRIDE;
-    const OffT *b = nb_bases<OffT>(tb) + (size_t)t * NB_STRIDE;
+__device__ __forceinline__ void load_nbhd(Nbhd<OffT> &h, const RowRegs &r, const uint64_t *nbb64, int t) {
 #pragma unroll
     for (int k = 0; k < 27; ++k) {
         const int s = nb_slot(k);
-        h.m[k] = s < 0 ? 0ull : m[s];
-        h.base[k] = s < 0 ? OffT(0) : b[s];
+        h.m[k] = s < 0 ? 0ull : r.mask(s);
+        if constexpr (std::is_same<OffT, uint32_t>::value) h.base[k] = s < 0 ? 0u : r.base32(s);
+        else h.base[k] = s < 0 ? 0ull : nbb64[(size_t)t * NB_STRIDE + s];
     }
 }
+constexpr int OWN = 13;  // the tile itself in its neighbourhood
 
 // where this lane's own values live
 template <bool RUNS, typename OffT>
@@ -196,12 +211,14 @@ struct Self {
     OffT stride;  // elements between directions: k (runs) or 64 (plain)
     int slot;     // this node's slot in each block
     int k;        // fluid nodes of the tile
-    __device__ __forceinline__ Self(const TileRec &r, int lane) {
-        base = (OffT)r.base;
-        k = __builtin_popcountll(r.mask);
+    __device__ __forceinline__ Self(const TileRec &r, int lane) : Self(r.mask, (OffT)r.base, lane) {}
+    __device__ __forceinline__ Self(const Nbhd<OffT> &h, int lane) : Self(h.m[OWN], h.base[OWN], lane) {}
+    __device__ __forceinline__ Self(uint64_t mask, OffT first, int lane) {
+        base = first;
+        k = __builtin_popcountll(mask);
         if constexpr (RUNS) {
             stride = (OffT)k;
-            slot = mbcnt(r.mask);
+            slot = mbcnt(mask);
         } else {
             stride = (OffT)TILE;
             slot = lane;
@@ -714,59 +731,76 @@ __device__ __forceinline__ void collide_mrt(T (&d)[Q], T rho_base, T omega, T Fx
 // Per tile the boundary buffer holds a mask of its boundary nodes and their
 // 64 codes: [n_tiles][9] uint64.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int axis_c(int a, int i) { return a == 0 ? CX[i] : (a == 1 ? CY[i] : CZ[i]); }
+constexpr int axis_c(int a, int i) { return a == 0 ? CX[i] : (a == 1 ? CY[i] : CZ[i]); }
 
-template <typename T, int INC>
-__device__ __forceinline__ void open_boundary(T (&d)[Q], const Phys &P, int t, int lane, T Fx, T Fy, T Fz) {
-    const uint64_t *rec = P.bc + 9 * (size_t)t;
-    const uint64_t any = rec[0];
-    if (!any) return;  // no boundary node in this tile
-    if (!lane_on(any)) return;
-    const int code = (int)reinterpret_cast<const uint8_t *>(rec + 1)[lane];
-    const int a = (code - 1) >> 2, r = (code - 1) & 3;
+// The rebuild at the nodes of one axis.  The axis is a template argument: with
+// a run-time axis the velocity components are read from a table in memory, one
+// load waited for after another (19 in a row at the end of a boundary tile's
+// gather: 20.4 us a step of a 101 x 61 x 47 channel, FP64, against 17.6 us).
+template <typename T, int INC, int A>
+__device__ __forceinline__ void open_boundary_axis(T (&d)[Q], const Phys &P, int r, T Fx, T Fy, T Fz) {
     const bool velocity = (r == 0 || r == 2);
     const int n = (r == 0 || r == 3) ? 1 : -1;  // c_a of the unknown populations
+    const bool up = n == 1;
     const T rb = T(P.rho_base);
     T s_tan = 0, s_known = 0, tx = 0, ty = 0, tz = 0;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        const int ca = axis_c(a, i);
-        if (ca == 0) {
+        if (axis_c(A, i) == 0) {
             s_tan += d[i];
             tx += T(CX[i]) * d[i];
             ty += T(CY[i]) * d[i];
             tz += T(CZ[i]) * d[i];
-        } else if (ca == -n) {
-            s_known += d[i];
+        } else if (axis_c(A, i) == -1) {
+            s_known += up ? d[i] : d[opposite(i)];
         }
     }
     s_tan += rb * T(2.0 / 3.0);
     s_known += rb * T(1.0 / 6.0);
-    const T Fa = a == 0 ? Fx : (a == 1 ? Fy : Fz);
+    const T Fa = A == 0 ? Fx : (A == 1 ? Fy : Fz);
     T Jx, Jy, Jz;
     if (velocity) {
         const T ux = T(P.bc_u[0]), uy = T(P.bc_u[1]), uz = T(P.bc_u[2]);
-        const T ua = a == 0 ? ux : (a == 1 ? uy : uz);
+        const T ua = A == 0 ? ux : (A == 1 ? uy : uz);
         const T rho = INC ? T(1) : (s_tan + T(2) * s_known - T(0.5) * T(n) * Fa) / (T(1) - T(n) * ua);
         Jx = rho * ux - T(0.5) * Fx;
         Jy = rho * uy - T(0.5) * Fy;
         Jz = rho * uz - T(0.5) * Fz;
     } else {
         const T Ja = T(n) * (T(P.bc_rho) - s_tan - T(2) * s_known);
-        Jx = a == 0 ? Ja : -T(0.5) * Fx;
-        Jy = a == 1 ? Ja : -T(0.5) * Fy;
-        Jz = a == 2 ? Ja : -T(0.5) * Fz;
+        Jx = A == 0 ? Ja : -T(0.5) * Fx;
+        Jy = A == 1 ? Ja : -T(0.5) * Fy;
+        Jz = A == 2 ? Ja : -T(0.5) * Fz;
     }
-    const T Nx = a == 0 ? T(0) : T(0.5) * tx - Jx * T(1.0 / 3.0);
-    const T Ny = a == 1 ? T(0) : T(0.5) * ty - Jy * T(1.0 / 3.0);
-    const T Nz = a == 2 ? T(0) : T(0.5) * tz - Jz * T(1.0 / 3.0);
-    // the unknowns' opposites (c_a = -n) are known and never rebuilt here
+    const T Nx = A == 0 ? T(0) : T(0.5) * tx - Jx * T(1.0 / 3.0);
+    const T Ny = A == 1 ? T(0) : T(0.5) * ty - Jy * T(1.0 / 3.0);
+    const T Nz = A == 2 ? T(0) : T(0.5) * tz - Jz * T(1.0 / 3.0);
+    // the unknowns (c_a = n) from their opposites (c_a = -n), which are known;
+    // i and j run over the pairs with c_a(i) = 1
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
-        if (axis_c(a, i) != n) continue;
+        if (axis_c(A, i) != 1) continue;
+        const int j = opposite(i);
         const T cJ = T(CX[i]) * Jx + T(CY[i]) * Jy + T(CZ[i]) * Jz;
-        d[i] = d[opposite(i)] + T(6.0 * weight(i)) * cJ - T(CX[i]) * Nx - T(CY[i]) * Ny - T(CZ[i]) * Nz;
+        const T di = d[i], dj = d[j];
+        const T vi = dj + T(6.0 * weight(i)) * cJ - T(CX[i]) * Nx - T(CY[i]) * Ny - T(CZ[i]) * Nz;
+        const T vj = di + T(6.0 * weight(i)) * -cJ - T(CX[j]) * Nx - T(CY[j]) * Ny - T(CZ[j]) * Nz;
+        d[i] = up ? vi : di;
+        d[j] = up ? dj : vj;
     }
+}
+
+// `any`: the tile's boundary nodes, `codes`: the codes of its 64 nodes
+template <typename T, int INC>
+__device__ __forceinline__ void open_boundary(T (&d)[Q], const Phys &P, uint64_t any, const uint8_t *codes, int lane,
+                                              T Fx, T Fy, T Fz) {
+    if (!any) return;  // no boundary node in this tile
+    if (!lane_on(any)) return;
+    const int code = (int)codes[lane];
+    const int a = (code - 1) >> 2, r = (code - 1) & 3;
+    if (a == 0) open_boundary_axis<T, INC, 0>(d, P, r, Fx, Fy, Fz);
+    else if (a == 1) open_boundary_axis<T, INC, 1>(d, P, r, Fx, Fy, Fz);
+    else open_boundary_axis<T, INC, 2>(d, P, r, Fx, Fy, Fz);
 }
 
 // the collision of a model: LBGK (0, 1) or multiple relaxation times (2, 3)
@@ -784,7 +818,7 @@ struct KArgs {
     char *dst;
     DevTables tb;
     int n_tiles;
-    int wpb;      // waves (tiles) per workgroup
+    int lw;       // log2 of the waves (tiles) per workgroup
     int nblocks;  // workgroups in the grid
     Phys P;
 };
@@ -795,60 +829,122 @@ struct FieldSlot {
     uint64_t base;  // entry offset of the tile's field run (wave-uniform)
     int k;          // fluid nodes of the tile
     int slot;
-    __device__ __forceinline__ FieldSlot(const DevTables &tb, int t, uint64_t mask) {
-        base = tb.fbase[t];
+    __device__ __forceinline__ FieldSlot(const DevTables &tb, int t, uint64_t mask) : FieldSlot(tb.fbase[t], mask) {}
+    __device__ __forceinline__ FieldSlot(uint64_t first, uint64_t mask) {
+        base = first;
         k = __builtin_popcountll(mask);
         slot = mbcnt(mask);
     }
     __device__ __forceinline__ uint64_t entry(int c) const { return base + (uint64_t)(c * k + slot); }
 };
 
+// a pointer read from memory is taken as one that may point to LDS unless its
+// type says global
+template <typename T>
+using GlobalConst = const __attribute__((address_space(1))) T *;
+
 // the per-node force field, one entry per fluid slot and component
 template <typename T>
-__device__ __forceinline__ void load_force(const Phys &P, const DevTables &tb, int t, uint64_t mask, T &Fx, T &Fy,
-                                           T &Fz) {
-    if (P.field) {
-        const FieldSlot fs(tb, t, mask);
-        const T *f = reinterpret_cast<const T *>(P.field);
+__device__ __forceinline__ void load_force(double F0, double F1, double F2, const void *field, uint64_t first,
+                                           uint64_t mask, T &Fx, T &Fy, T &Fz) {
+    Fx = T(F0);
+    Fy = T(F1);
+    Fz = T(F2);
+    if (field) {
+        const FieldSlot fs(first, mask);
+        const GlobalConst<T> f = (GlobalConst<T>)reinterpret_cast<const T *>(field);
         Fx = f[fs.entry(0)];
         Fy = f[fs.entry(1)];
         Fz = f[fs.entry(2)];
-    } else {
-        Fx = T(P.F[0]);
-        Fy = T(P.F[1]);
-        Fz = T(P.F[2]);
     }
+}
+
+template <typename T>
+__device__ __forceinline__ void load_force(const Phys &P, uint64_t first, uint64_t mask, T &Fx, T &Fy, T &Fz) {
+    load_force<T>(P.F[0], P.F[1], P.F[2], P.field, first, mask, Fx, Fy, Fz);
 }
 
 // ---------------------------------------------------------------------------
 // the fused step (Alg. 2): gather with bounce-back, collide, store
 // ---------------------------------------------------------------------------
-template <int ST, int MODEL, typename OffT>
-__global__ __launch_bounds__(512) void k_step(KArgs a) {
+// The physics of a step, a kernel's last argument, OFF bytes into its
+// arguments, read where this is called: after the gather's loads are issued and
+// before the first of them is waited for.  Left to itself the compiler reads
+// the arguments on entry, where they wait in scalar registers through the
+// gather, which has none to spare, or where they are used, which puts a read
+// of the argument buffer after the gather.
+template <int OFF>
+struct StepPhys {
+    typedef const __attribute__((address_space(4))) char *ConstPtr;
+    typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
+    ConstPtr at;
+    u32x16 v;  // Phys bytes 0..63
+    u32x4s w;  // and 64..79
+    __device__ __forceinline__ StepPhys() {
+        at = (ConstPtr)__builtin_amdgcn_kernarg_segment_ptr() + OFF;
+        asm volatile("" : "+s"(at));
+        v = *(const __attribute__((address_space(4))) u32x16 *)at;
+        w = *(const __attribute__((address_space(4))) u32x4s *)(at + 64);
+        asm volatile("" : "+s"(v), "+s"(w));
+    }
+    __device__ __forceinline__ double f64(int byte) const {
+        return __builtin_bit_cast(double, v[byte / 4] | (uint64_t)v[byte / 4 + 1] << 32);
+    }
+    __device__ __forceinline__ double omega() const { return f64(offsetof(Phys, omega)); }
+    __device__ __forceinline__ double kg() const { return f64(offsetof(Phys, kg)); }
+    __device__ __forceinline__ double rho_base() const { return f64(offsetof(Phys, rho_base)); }
+    __device__ __forceinline__ double F(int c) const { return f64(offsetof(Phys, F) + 8 * c); }
+    __device__ __forceinline__ const void *field() const {
+        static_assert(offsetof(Phys, F) == 40 && offsetof(Phys, field) == 64 && offsetof(Phys, scale) == 72 &&
+                          offsetof(Phys, inv_scale) == 76,
+                      "the fields a step reads");
+        return (const void *)(w[0] | (uint64_t)w[1] << 32);
+    }
+    // by way of a scalar: a bit cast of a vector's element reads element 0
+    __device__ __forceinline__ float f32(int i) const {
+        const uint32_t bits = w[i];
+        return __builtin_bit_cast(float, bits);
+    }
+    __device__ __forceinline__ float scale() const { return f32(2); }
+    __device__ __forceinline__ float inv_scale() const { return f32(3); }
+    __device__ __forceinline__ const Phys &all() const { return *(const Phys *)at; }
+};
+// bytes of the arguments before it: row, nbb64, src, dst, n_tiles, lw,
+// nblocks, counter (and the boundary buffer)
+constexpr int STOCHASTIC = 16;  // flag beside lw in a step's shape argument
+constexpr int HOT_BYTES = 4 * 8 + 4 * 4;
+
+template <int ST, int MODEL, typename OffT, bool OPEN>
+__device__ __forceinline__ void step_tile(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst,
+                                          int n_tiles, int shape, int nblocks, uint32_t counter, const uint64_t *bc) {
     using C = Codec<ST>;
     using S = typename C::S;
     using T = typename C::T;
     constexpr bool RN = C::RUNS;
-    const int tw = wave_tile<!RN>(a.wpb, a.nblocks);
-    if (tw >= a.n_tiles) return;
+    const int tw = wave_tile<!RN>(shape & (STOCHASTIC - 1), nblocks);
+    if (tw >= n_tiles) return;
     // consecutive launches walk the tiles in opposite directions, so a step
     // starts on the tiles the previous one wrote last (FP16 166.7 -> 164.6 us
     // on a 256^3 sphere pack, FP64 389.2 -> 388.5 us, FP32 unchanged); the
     // order of the tiles within a step does not change any result
-    const int t = (a.P.launch_counter & 1u) ? a.n_tiles - 1 - tw : tw;
+    const int t = (counter & 1u) ? n_tiles - 1 - tw : tw;
     const int lane = (int)(threadIdx.x & 63);
-    const TileRec rec = a.tb.rec[t];
-    // the tile's position (keys the stochastic rounding), read with its record
+    uint64_t any = 0;  // the tile's boundary nodes
+    if constexpr (OPEN) any = bc[9 * (size_t)t];
+    const RowRegs r(row, t);
+    Nbhd<OffT> h;
+    load_nbhd(h, r, nbb64, t);
+    const uint64_t fbase = r.fbase();
+    // the tile's position keys the stochastic rounding
     uint32_t cx = 0, cy = 0, cz = 0;
     if constexpr (ST == LBM_F16S) {
-        const int32_t *c = a.tb.xyz + 4 * (size_t)t;
-        cx = (uint32_t)c[0];
-        cy = (uint32_t)c[1];
-        cz = (uint32_t)c[2];
+        cx = r.xyz(0);
+        cy = r.xyz(1);
+        cz = r.xyz(2);
     }
-    const uint64_t own = rec.mask;
+    const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
-    const Self<RN, OffT> me(rec, lane);
+    const Self<RN, OffT> me(h, lane);
     T d[Q];
     if constexpr (!RN) {
         // solid lanes of the plain layout store zeros: encode 0 (exact in
@@ -857,59 +953,78 @@ __global__ __launch_bounds__(512) void k_step(KArgs a) {
         for (int i = 0; i < Q; ++i) d[i] = T(0);
     }
     if (fl) {  // solid nodes neither gather nor collide
-        Nbhd<OffT> h;
-        load_nbhd(h, a.tb, t);
         S raw[Q];
-        gather_all<false, RN, S, OffT>(raw, h, a.src, me, lane);
+        gather_all<false, RN, S, OffT>(raw, h, src, me, lane);
+        const StepPhys<HOT_BYTES + (OPEN ? 8 : 0)> P;
+        const uint8_t *codes = OPEN ? reinterpret_cast<const uint8_t *>(bc + 9 * (size_t)t + 1) : nullptr;
         T Fx, Fy, Fz;
-        load_force<T>(a.P, a.tb, t, own, Fx, Fy, Fz);
+        load_force<T>(P.F(0), P.F(1), P.F(2), P.field(), fbase, own, Fx, Fy, Fz);
         if constexpr (C::SCALED) {
 #pragma unroll
             for (int i = 0; i < Q; ++i) d[i] = C::dec_scaled(raw[i]);
-            if (a.P.bc) {  // the rebuild works at unit scale (exact round trip)
+            if constexpr (OPEN) {  // the rebuild works at unit scale (exact round trip)
 #pragma unroll
-                for (int i = 0; i < Q; ++i) d[i] *= a.P.inv_scale;
-                open_boundary<T, (MODEL & 1)>(d, a.P, t, lane, Fx, Fy, Fz);
+                for (int i = 0; i < Q; ++i) d[i] *= P.inv_scale();
+                open_boundary<T, (MODEL & 1)>(d, P.all(), any, codes, lane, Fx, Fy, Fz);
 #pragma unroll
-                for (int i = 0; i < Q; ++i) d[i] *= a.P.scale;
+                for (int i = 0; i < Q; ++i) d[i] *= P.scale();
             }
-            collide_model<T, MODEL, true>(d, T(a.P.rho_base), T(a.P.omega), T(a.P.kg), Fx, Fy, Fz, T(a.P.scale),
-                                          T(a.P.inv_scale));
+            collide_model<T, MODEL, true>(d, T(P.rho_base()), T(P.omega()), T(P.kg()), Fx, Fy, Fz, T(P.scale()),
+                                          T(P.inv_scale()));
         } else {
 #pragma unroll
-            for (int i = 0; i < Q; ++i) d[i] = C::dec(raw[i], a.P.inv_scale);
-            if (a.P.bc) open_boundary<T, (MODEL & 1)>(d, a.P, t, lane, Fx, Fy, Fz);
-            collide_model<T, MODEL>(d, T(a.P.rho_base), T(a.P.omega), T(a.P.kg), Fx, Fy, Fz);
+            for (int i = 0; i < Q; ++i) d[i] = C::dec(raw[i], 1.0f);
+            if constexpr (OPEN) open_boundary<T, (MODEL & 1)>(d, P.all(), any, codes, lane, Fx, Fy, Fz);
+            collide_model<T, MODEL>(d, T(P.rho_base()), T(P.omega()), T(P.kg()), Fx, Fy, Fz);
         }
     }
     if constexpr (ST == LBM_F16S) {
-        if (a.P.f16_stochastic) {
+        if (shape & STOCHASTIC) {
             // keyed on the node's position, not on where the tile is stored
-            const uint32_t tile_seed = hash32(cx + hash32(cy + hash32(cz + hash32(a.P.launch_counter))));
+            const uint32_t tile_seed = hash32(cx + hash32(cy + hash32(cz + hash32(counter))));
             const uint32_t seed = hash32(tile_seed + (uint32_t)lane);
             typename C::Pair pair = {};
-            store_tile<S, RN, OffT, true, !RN>(a.dst, me, own, fl, lane, [&](int i) {
+            store_tile<S, RN, OffT, true, !RN>(dst, me, own, fl, lane, [&](int i) {
                 return C::enc_sr_scaled(d[i], seed + (uint32_t)i * 0x9E3779B9u, pair);
             });
             return;
         }
-        store_tile<S, RN, OffT, true, !RN>(a.dst, me, own, fl, lane, [&](int i) { return C::enc_scaled(d[i]); });
+        store_tile<S, RN, OffT, true, !RN>(dst, me, own, fl, lane, [&](int i) { return C::enc_scaled(d[i]); });
     } else {
-        store_tile<S, RN, OffT, true, !RN>(a.dst, me, own, fl, lane, [&](int i) { return C::enc(d[i], a.P.scale); });
+        store_tile<S, RN, OffT, true, !RN>(dst, me, own, fl, lane, [&](int i) { return C::enc(d[i], 1.0f); });
     }
+}
+
+// Open boundaries have a kernel of their own: in one kernel their parameters
+// and lane masks took scalar registers from every other step (12-16 spilled to
+// vector lanes, 6 without them).
+template <int ST, int MODEL, typename OffT>
+__global__ __launch_bounds__(512) void k_step(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst,
+                                              int n_tiles, int shape, int nblocks, uint32_t counter, Phys P) {
+    step_tile<ST, MODEL, OffT, false>(row, nbb64, src, dst, n_tiles, shape, nblocks, counter, nullptr);
+}
+
+template <int ST, int MODEL, typename OffT>
+__global__ __launch_bounds__(512) void k_step_open(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst,
+                                                   int n_tiles, int shape, int nblocks, uint32_t counter,
+                                                   const uint64_t *bc, Phys P) {
+    step_tile<ST, MODEL, OffT, true>(row, nbb64, src, dst, n_tiles, shape, nblocks, counter, bc);
 }
 
 // the paper's measurement kernels (Section 4.1): kind 1 "read/write only",
 // kind 2 "propagation only"
 template <typename S, bool RN, int KIND, typename OffT>
-__global__ __launch_bounds__(512) void k_calib(KArgs a) {
-    const int t = wave_tile<!RN>(a.wpb, a.nblocks);
-    if (t >= a.n_tiles) return;
+__global__ __launch_bounds__(512) void k_calib(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst, int n_tiles,
+                                               int lw, int nblocks) {
+    const int t = wave_tile<!RN>(lw, nblocks);
+    if (t >= n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
-    const TileRec rec = a.tb.rec[t];
-    const uint64_t own = rec.mask;
+    const RowRegs r(row, t);
+    Nbhd<OffT> h;
+    load_nbhd(h, r, nbb64, t);
+    const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
-    const Self<RN, OffT> me(rec, lane);
+    const Self<RN, OffT> me(h, lane);
     S v[Q];
     if constexpr (!RN) {
         // whole-block stores write the solid lanes too: zeros, as the step does
@@ -919,14 +1034,12 @@ __global__ __launch_bounds__(512) void k_calib(KArgs a) {
     if (fl) {
         if constexpr (KIND == 1) {
 #pragma unroll
-            for (int i = 0; i < Q; ++i) v[i] = load_elem<OffT, S>(a.src, me.elem(i));
+            for (int i = 0; i < Q; ++i) v[i] = load_elem<OffT, S>(src, me.elem(i));
         } else {
-            Nbhd<OffT> h;
-            load_nbhd(h, a.tb, t);
-            gather_all<false, RN, S, OffT>(v, h, a.src, me, lane);
+            gather_all<false, RN, S, OffT>(v, h, src, me, lane);
         }
     }
-    store_tile<S, RN, OffT, true>(a.dst, me, own, fl, lane, [&](int i) { return v[i]; });
+    store_tile<S, RN, OffT, true>(dst, me, own, fl, lane, [&](int i) { return v[i]; });
 }
 
 // The paper's intra-tile layout study (Section 3.3, Eqs. 11-13; Table 5):
@@ -980,18 +1093,18 @@ __device__ __forceinline__ void gather_layout_all(S (&v)[Q], const Nbhd<OffT> &h
 }
 
 template <typename S, int LS, typename OffT>
-__global__ __launch_bounds__(512) void k_calib_layout(KArgs a) {
-    const int t = wave_tile(a.wpb, a.nblocks);
-    if (t >= a.n_tiles) return;
+__global__ __launch_bounds__(512) void k_calib_layout(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst, int n_tiles,
+                                               int lw, int nblocks) {
+    const int t = wave_tile(lw, nblocks);
+    if (t >= n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const int x = lane & 3, y = (lane >> 2) & 3, z = lane >> 4;
-    const TileRec rec = a.tb.rec[t];
-    const Self<false, OffT> me(rec, lane);
     Nbhd<OffT> h;
-    load_nbhd(h, a.tb, t);
+    load_nbhd(h, RowRegs(row, t), nbb64, t);
+    const Self<false, OffT> me(h, lane);
     S v[Q];
-    gather_layout_all<LS, S, OffT>(v, h, a.src, me, x, y, z, lane, std::make_integer_sequence<int, Q>{});
-    S *out = reinterpret_cast<S *>(a.dst);
+    gather_layout_all<LS, S, OffT>(v, h, src, me, x, y, z, lane, std::make_integer_sequence<int, Q>{});
+    S *out = reinterpret_cast<S *>(dst);
 #pragma unroll
     for (int i = 0; i < Q; ++i) store_stream(out + (me.base + (OffT)(i * TILE + layout_slot(LS, i, x, y, z))), v[i]);
 }
@@ -1004,7 +1117,7 @@ template <int ST>
 __global__ __launch_bounds__(512) void k_init(KArgs a, char *b, double ux, double uy, double uz) {
     using C = Codec<ST>;
     using S = typename C::S;
-    const int t = wave_tile(a.wpb, a.nblocks);
+    const int t = wave_tile(a.lw, a.nblocks);
     if (t >= a.n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const TileRec rec = a.tb.rec[t];
@@ -1063,7 +1176,7 @@ __global__ __launch_bounds__(512) void k_macro(KArgs a, double *rho_out, double 
     using C = Codec<ST>;
     using S = typename C::S;
     using T = typename C::T;
-    const int t = wave_tile(a.wpb, a.nblocks);
+    const int t = wave_tile(a.lw, a.nblocks);
     if (t >= a.n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const TileRec rec = a.tb.rec[t];
@@ -1081,7 +1194,7 @@ __global__ __launch_bounds__(512) void k_macro(KArgs a, double *rho_out, double 
         }
     }
     T Fx = T(0), Fy = T(0), Fz = T(0);
-    if (fl) load_force<T>(a.P, a.tb, t, rec.mask, Fx, Fy, Fz);
+    if (fl) load_force<T>(a.P, a.P.field ? a.tb.fbase[t] : 0, rec.mask, Fx, Fy, Fz);
     const double rho = a.P.rho_base + drho;
     const double mx = jx - 0.5 * (double)Fx, my = jy - 0.5 * (double)Fy, mz = jz - 0.5 * (double)Fz;
     double ux = mx, uy = my, uz = mz;
@@ -1158,7 +1271,7 @@ template <int ST>
 __global__ __launch_bounds__(512) void k_get_state(KArgs a, double *dense, int nx, int ny, int nz) {
     using C = Codec<ST>;
     using S = typename C::S;
-    const int t = wave_tile(a.wpb, a.nblocks);
+    const int t = wave_tile(a.lw, a.nblocks);
     if (t >= a.n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const TileRec rec = a.tb.rec[t];
@@ -1177,7 +1290,7 @@ __global__ __launch_bounds__(512) void k_set_state(KArgs a, const double *dense,
     using C = Codec<ST>;
     using S = typename C::S;
     using T = typename C::T;
-    const int t = wave_tile(a.wpb, a.nblocks);
+    const int t = wave_tile(a.lw, a.nblocks);
     if (t >= a.n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const TileRec rec = a.tb.rec[t];
@@ -1201,7 +1314,7 @@ __global__ __launch_bounds__(512) void k_set_state(KArgs a, const double *dense,
 // fluid slot; the pad entries after a tile's 3k are set to 0
 template <typename T>
 __global__ __launch_bounds__(512) void k_force_to_tiles(KArgs a, const double *g, T *out, int nx, int ny, int nz) {
-    const int t = wave_tile(a.wpb, a.nblocks);
+    const int t = wave_tile(a.lw, a.nblocks);
     if (t >= a.n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const uint64_t mask = a.tb.rec[t].mask;
@@ -1219,7 +1332,7 @@ __global__ __launch_bounds__(512) void k_force_to_tiles(KArgs a, const double *g
 // per-fluid-slot field [3 components] -> dense FP64 [3][nz][ny][nx]
 template <typename T>
 __global__ __launch_bounds__(512) void k_field_to_dense(KArgs a, const T *in, double *dense, int nx, int ny, int nz) {
-    const int t = wave_tile(a.wpb, a.nblocks);
+    const int t = wave_tile(a.lw, a.nblocks);
     if (t >= a.n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const uint64_t mask = a.tb.rec[t].mask;
@@ -1234,7 +1347,7 @@ __global__ __launch_bounds__(512) void k_field_to_dense(KArgs a, const T *in, do
 template <typename T>
 __global__ __launch_bounds__(512) void k_tiles_to_dense(KArgs a, const T *in, int ncomp, double *dense, int nx, int ny,
                                                        int nz) {
-    const int t = wave_tile(a.wpb, a.nblocks);
+    const int t = wave_tile(a.lw, a.nblocks);
     if (t >= a.n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const bool fl = (a.tb.rec[t].mask >> lane) & 1;
@@ -1399,17 +1512,18 @@ __device__ __forceinline__ void collide_jt_model(const T (&d)[Q], T rho_base, co
         collide_jt<T, (MODEL & 1)>(d, rho_base, lam, omega, kg, Fx, Fy, Fz, eta, gx, gy, gz);
 }
 
+// The first arguments, twelve registers, are what a wave needs before it can
+// issue its gathers: the build has them preloaded.
 struct AdjArgs {
-    const char *s;      // forward lattice feeding the forward gather
-    const char *eta_in; // adjoint lattice feeding the reverse gather
     char *out;          // adjoint lattice written
     double *grad;       // dL/dg, FP64 per fluid slot (the force field's layout)
-    DevTables tb;
-    int n_tiles;
-    int wpb;
-    int nblocks;
     Phys P;
 };
+//   s       forward lattice feeding the forward gather
+//   eta_in  adjoint lattice feeding the reverse gather
+#define ADJ_PARAMS                                                                                                 \
+    const NbRow *row, const uint64_t *nbb64, const char *s, const char *eta_in, int n_tiles, int lw, int nblocks, \
+        uint32_t counter, AdjArgs a
 
 // seed: from s_{T-1}: g_T = S s_{T-1}, s_T = C(g_T), lam_T = dL/ds_T,
 // eta_T = J_T^T lam_T, grad = rho0 [(dC/dF)^T lam_T + dL/dF].  With
@@ -1420,40 +1534,41 @@ struct AdjWaves;
 
 template <int ST, int MODEL, typename OffT>
 __global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(1, AdjWaves<ST, MODEL, OffT>::max))) void k_adj_seed(AdjArgs a) {
+__attribute__((amdgpu_waves_per_eu(1, AdjWaves<ST, MODEL, OffT>::max))) void k_adj_seed(ADJ_PARAMS) {
     constexpr int INC = MODEL & 1;
     using T = typename Codec<ST>::S;
-    const int t = wave_tile(a.wpb, a.nblocks);
-    if (t >= a.n_tiles) return;
+    const int t = wave_tile(lw, nblocks);
+    if (t >= n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
-    const TileRec rec = a.tb.rec[t];
-    const uint64_t own = rec.mask;
+    const RowRegs r(row, t);
+    Nbhd<OffT> h;
+    load_nbhd(h, r, nbb64, t);
+    const uint64_t fbase = r.fbase();
+    const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
-    const Self<true, OffT> me(rec, lane);
+    const Self<true, OffT> me(h, lane);
     const T rb = T(a.P.rho_base), om = T(a.P.omega), kg = T(a.P.kg), inv_n = T(a.P.inv_nfluid);
     T eta[Q], gx = 0, gy = 0, gz = 0;
     if (fl) {
-        Nbhd<OffT> h;
-        load_nbhd(h, a.tb, t);
         T g[Q];
-        gather_all<false, true, T, OffT>(g, h, a.s, me, lane);
+        gather_all<false, true, T, OffT>(g, h, s, me, lane);
         T Fx, Fy, Fz;
-        load_force<T>(a.P, a.tb, t, own, Fx, Fy, Fz);
+        load_force<T>(a.P, fbase, own, Fx, Fy, Fz);
         T lam[Q];
         T irT = T(1);
         if constexpr (INC) {
 #pragma unroll
             for (int i = 0; i < Q; ++i) lam[i] = T(CX[i]) * inv_n;
         } else {
-            T s[Q];
+            T st[Q];
 #pragma unroll
-            for (int i = 0; i < Q; ++i) s[i] = g[i];
-            collide_model<T, MODEL>(s, rb, om, kg, Fx, Fy, Fz);
+            for (int i = 0; i < Q; ++i) st[i] = g[i];
+            collide_model<T, MODEL>(st, rb, om, kg, Fx, Fy, Fz);
             T drT = 0, jx = 0;
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
-                drT += s[i];
-                jx += T(CX[i]) * s[i];
+                drT += st[i];
+                jx += T(CX[i]) * st[i];
             }
             irT = T(1) / (rb + drT);
             const T uxT = (jx - T(0.5) * Fx) * irT;
@@ -1464,7 +1579,7 @@ __attribute__((amdgpu_waves_per_eu(1, AdjWaves<ST, MODEL, OffT>::max))) void k_a
         gx += T(-0.5) * irT * inv_n;
     }
     store_tile<T, true, OffT, true>(a.out, me, own, fl, lane, [&](int i) { return eta[i]; });
-    const FieldSlot fs(a.tb, t, own);
+    const FieldSlot fs(fbase, own);
     if (fl) {
         a.grad[fs.entry(0)] = a.P.rho0 * (double)gx;
         a.grad[fs.entry(1)] = a.P.rho0 * (double)gy;
@@ -1497,22 +1612,24 @@ struct AdjWaves {
 template <int ST, int MODEL, typename OffT>
 __global__ __launch_bounds__(512)
 __attribute__((amdgpu_waves_per_eu(AdjWaves<ST, MODEL, OffT>::value, AdjWaves<ST, MODEL, OffT>::max))) void k_adj_step(
-    AdjArgs a) {
+    ADJ_PARAMS) {
     using T = typename Codec<ST>::S;
-    const int tw = wave_tile(a.wpb, a.nblocks);
-    if (tw >= a.n_tiles) return;
+    const int tw = wave_tile(lw, nblocks);
+    if (tw >= n_tiles) return;
     // consecutive adjoint launches walk the tiles in opposite directions, as
     // the forward steps do (FP64 LBGK 112.5 -> 109.5 us, LBMRT 120.0 -> 115.7
     // us on a 128^3 sphere pack; FP32 unchanged)
-    const int t = (a.P.launch_counter & 1u) ? a.n_tiles - 1 - tw : tw;
+    const int t = (counter & 1u) ? n_tiles - 1 - tw : tw;
     const int lane = (int)(threadIdx.x & 63);
-    const TileRec rec = a.tb.rec[t];
-    const uint64_t own = rec.mask;
+    const RowRegs r(row, t);
+    Nbhd<OffT> h;
+    load_nbhd(h, r, nbb64, t);
+    const uint64_t fbase = r.fbase();
+    const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
-    const Self<true, OffT> me(rec, lane);
+    const Self<true, OffT> me(h, lane);
     T eta[Q];
     if (fl) {
-        Nbhd<OffT> h;
         T lam[Q], g[Q];
         T Fx, Fy, Fz;
         T gx, gy, gz;
@@ -1521,23 +1638,21 @@ __attribute__((amdgpu_waves_per_eu(AdjWaves<ST, MODEL, OffT>::value, AdjWaves<ST
             // gather: their loads go first and are in flight with it (LBGK
             // 117.9 -> 117.1 us, incompressible 116.6 -> 114.8, LBMRT 130.0
             // -> 123.7 on a 128^3 sphere pack; FP32 gains nothing from it)
-            const FieldSlot fs(a.tb, t, own);
+            const FieldSlot fs(fbase, own);
             const double g0 = a.grad[fs.entry(0)], g1 = a.grad[fs.entry(1)], g2 = a.grad[fs.entry(2)];
-            load_force<T>(a.P, a.tb, t, own, Fx, Fy, Fz);
-            load_nbhd(h, a.tb, t);
-            gather_pairs<true, T, OffT>(lam, g, h, a.eta_in, a.s, me, lane);
+            load_force<T>(a.P, fbase, own, Fx, Fy, Fz);
+            gather_pairs<true, T, OffT>(lam, g, h, eta_in, s, me, lane);
             collide_jt_model<T, MODEL>(g, T(a.P.rho_base), lam, T(a.P.omega), T(a.P.kg), Fx, Fy, Fz, eta, gx, gy,
                                        gz);
             a.grad[fs.entry(0)] = g0 + a.P.rho0 * (double)gx;
             a.grad[fs.entry(1)] = g1 + a.P.rho0 * (double)gy;
             a.grad[fs.entry(2)] = g2 + a.P.rho0 * (double)gz;
         } else {
-            load_nbhd(h, a.tb, t);
-            gather_pairs<true, T, OffT>(lam, g, h, a.eta_in, a.s, me, lane);
-            load_force<T>(a.P, a.tb, t, own, Fx, Fy, Fz);
+            gather_pairs<true, T, OffT>(lam, g, h, eta_in, s, me, lane);
+            load_force<T>(a.P, fbase, own, Fx, Fy, Fz);
             collide_jt_model<T, MODEL>(g, T(a.P.rho_base), lam, T(a.P.omega), T(a.P.kg), Fx, Fy, Fz, eta, gx, gy,
                                        gz);
-            const FieldSlot fs(a.tb, t, own);
+            const FieldSlot fs(fbase, own);
             a.grad[fs.entry(0)] += a.P.rho0 * (double)gx;
             a.grad[fs.entry(1)] += a.P.rho0 * (double)gy;
             a.grad[fs.entry(2)] += a.P.rho0 * (double)gz;
@@ -1548,20 +1663,20 @@ __attribute__((amdgpu_waves_per_eu(AdjWaves<ST, MODEL, OffT>::value, AdjWaves<ST
 
 // final: lam_0 = S^T eta_1
 template <int ST, int MODEL, typename OffT>
-__global__ __launch_bounds__(512) void k_adj_final(AdjArgs a) {
+__global__ __launch_bounds__(512) void k_adj_final(ADJ_PARAMS) {
     using T = typename Codec<ST>::S;
-    const int t = wave_tile(a.wpb, a.nblocks);
-    if (t >= a.n_tiles) return;
+    const int t = wave_tile(lw, nblocks);
+    if (t >= n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
-    const TileRec rec = a.tb.rec[t];
-    const uint64_t own = rec.mask;
+    const RowRegs r(row, t);
+    Nbhd<OffT> h;
+    load_nbhd(h, r, nbb64, t);
+    const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
-    const Self<true, OffT> me(rec, lane);
+    const Self<true, OffT> me(h, lane);
     T lam[Q];
     if (fl) {
-        Nbhd<OffT> h;
-        load_nbhd(h, a.tb, t);
-        gather_all<true, true, T, OffT>(lam, h, a.eta_in, me, lane);
+        gather_all<true, true, T, OffT>(lam, h, eta_in, me, lane);
     }
     store_tile<T, true, OffT, false>(a.out, me, own, fl, lane, [&](int i) { return lam[i]; });
 }
@@ -1632,21 +1747,35 @@ static KArgs make_args(const Launch &L, const Phys &P, const void *src, void *ds
     a.dst = reinterpret_cast<char *>(dst);
     a.tb = L.tb;
     a.n_tiles = L.n_tiles;
-    a.wpb = L.tpw;
+    a.lw = __builtin_ctz((unsigned)L.tpw);
     a.nblocks = L.grid;
     a.P = P;
     return a;
 }
 
+// The arguments that a wave needs before it can issue its gathers, the first
+// of every kernel that gathers: the build has the command processor preload
+// the first twelve argument registers (-amdgpu-kernarg-preload-count), so they
+// are in scalar registers when a wave starts instead of a memory read away.
+#define KHOT(a) (a).tb.row, (a).tb.nbb64, (a).src, (a).dst, (a).n_tiles, (a).lw, (a).nblocks
+
 static dim3 block_of(const Launch &L) { return dim3(64 * L.tpw); }
+
+template <int ST, int MODEL, typename OffT>
+static hipError_t step_o(const Launch &L, KArgs a) {
+    if (a.P.f16_stochastic) a.lw |= STOCHASTIC;
+    if (a.P.bc)
+        hipLaunchKernelGGL((k_step_open<ST, MODEL, OffT>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a),
+                           a.P.launch_counter, a.P.bc, a.P);
+    else
+        hipLaunchKernelGGL((k_step<ST, MODEL, OffT>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a),
+                           a.P.launch_counter, a.P);
+    return hipGetLastError();
+}
 
 template <int ST, int MODEL>
 static hipError_t step_t(const Launch &L, const KArgs &a) {
-    if (L.off32)
-        hipLaunchKernelGGL((k_step<ST, MODEL, uint32_t>), dim3(L.grid), block_of(L), 0, L.stream, a);
-    else
-        hipLaunchKernelGGL((k_step<ST, MODEL, uint64_t>), dim3(L.grid), block_of(L), 0, L.stream, a);
-    return hipGetLastError();
+    return L.off32 ? step_o<ST, MODEL, uint32_t>(L, a) : step_o<ST, MODEL, uint64_t>(L, a);
 }
 
 template <int ST>
@@ -1675,18 +1804,18 @@ template <int ST, int KIND>
 static hipError_t calib_t(const Launch &L, const KArgs &a) {
     using C = Codec<ST>;
     if (L.off32)
-        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint32_t>), dim3(L.grid), block_of(L), 0, L.stream, a);
+        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint32_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a));
     else
-        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint64_t>), dim3(L.grid), block_of(L), 0, L.stream, a);
+        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint64_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a));
     return hipGetLastError();
 }
 
 template <typename S, int LS>
 static hipError_t calib_layout_t(const Launch &L, const KArgs &a) {
     if (L.off32)
-        hipLaunchKernelGGL((k_calib_layout<S, LS, uint32_t>), dim3(L.grid), block_of(L), 0, L.stream, a);
+        hipLaunchKernelGGL((k_calib_layout<S, LS, uint32_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a));
     else
-        hipLaunchKernelGGL((k_calib_layout<S, LS, uint64_t>), dim3(L.grid), block_of(L), 0, L.stream, a);
+        hipLaunchKernelGGL((k_calib_layout<S, LS, uint64_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a));
     return hipGetLastError();
 }
 
@@ -1818,20 +1947,6 @@ hipError_t launch_tiles_to_dense(const Launch &L, const void *tile_buf, int ncom
     return hipGetLastError();
 }
 
-static AdjArgs make_adj(const Launch &L, const Phys &P, const void *s, const void *eta_in, void *out, double *grad) {
-    AdjArgs a;
-    a.s = reinterpret_cast<const char *>(s);
-    a.eta_in = reinterpret_cast<const char *>(eta_in);
-    a.out = reinterpret_cast<char *>(out);
-    a.grad = grad;
-    a.tb = L.tb;
-    a.n_tiles = L.n_tiles;
-    a.wpb = L.tpw;
-    a.nblocks = L.grid;
-    a.P = P;
-    return a;
-}
-
 // the adjoint kernels exist for FP64 and FP32 storage (runs layout) and every
 // model; the final reverse gather has no model
 template <int ST, int MODEL, typename OffT>
@@ -1847,39 +1962,48 @@ struct FinalK {
     static constexpr auto fn = k_adj_final<ST, LBM_QUASI_COMPRESSIBLE, OffT>;
 };
 
+using AdjFn = void (*)(ADJ_PARAMS);
+
 template <template <int, int, typename> class K, int MODEL>
-static void (*adj_fn(const Launch &L, bool f32))(AdjArgs) {
+static AdjFn adj_fn(const Launch &L, bool f32) {
     if (L.off32) return f32 ? K<LBM_F32, MODEL, uint32_t>::fn : K<LBM_F64, MODEL, uint32_t>::fn;
     return f32 ? K<LBM_F32, MODEL, uint64_t>::fn : K<LBM_F64, MODEL, uint64_t>::fn;
 }
 
 template <template <int, int, typename> class K>
-static hipError_t launch_adj(const Launch &L, const AdjArgs &a) {
+static hipError_t launch_adj(const Launch &L, const Phys &P, const void *s, const void *eta_in, void *out,
+                             double *grad) {
     if (L.n_tiles == 0) return hipSuccess;
-    const bool f32 = a.P.storage == LBM_F32;
-    void (*fn)(AdjArgs) = nullptr;
-    switch (a.P.model) {
+    const bool f32 = P.storage == LBM_F32;
+    AdjFn fn = nullptr;
+    switch (P.model) {
     case LBM_QUASI_COMPRESSIBLE: fn = adj_fn<K, LBM_QUASI_COMPRESSIBLE>(L, f32); break;
     case LBM_INCOMPRESSIBLE: fn = adj_fn<K, LBM_INCOMPRESSIBLE>(L, f32); break;
     case LBM_MRT_QUASI_COMPRESSIBLE: fn = adj_fn<K, LBM_MRT_QUASI_COMPRESSIBLE>(L, f32); break;
     case LBM_MRT_INCOMPRESSIBLE: fn = adj_fn<K, LBM_MRT_INCOMPRESSIBLE>(L, f32); break;
     default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), 0, L.stream, a);
+    AdjArgs a;
+    a.out = reinterpret_cast<char *>(out);
+    a.grad = grad;
+    a.P = P;
+    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), 0, L.stream, L.tb.row, L.tb.nbb64,
+                       reinterpret_cast<const char *>(s), reinterpret_cast<const char *>(eta_in), L.n_tiles,
+                       __builtin_ctz((unsigned)L.tpw), L.grid, P.launch_counter, a);
     return hipGetLastError();
 }
 
 hipError_t launch_adjoint_seed(const Launch &L, const Phys &P, const void *s_prev, void *eta, double *grad) {
-    return launch_adj<SeedK>(L, make_adj(L, P, s_prev, nullptr, eta, grad));
+    return launch_adj<SeedK>(L, P, s_prev, nullptr, eta, grad);
 }
 
 hipError_t launch_adjoint_step(const Launch &L, const Phys &P, const void *s_prev2, const void *eta_in, void *eta_out,
                                double *grad) {
-    return launch_adj<StepK>(L, make_adj(L, P, s_prev2, eta_in, eta_out, grad));
+    return launch_adj<StepK>(L, P, s_prev2, eta_in, eta_out, grad);
 }
 
 hipError_t launch_adjoint_final(const Launch &L, const Phys &P, const void *eta_in, void *lambda_out) {
-    return launch_adj<FinalK>(L, make_adj(L, P, nullptr, eta_in, lambda_out, nullptr));
+    return launch_adj<FinalK>(L, P, nullptr, eta_in, lambda_out, nullptr);
 }
 
 }  // namespace tlbm
