@@ -261,7 +261,7 @@ extern "C" int lbm_required_bytes(const lbm_tiles *tiles, const lbm_params *para
     if (!out) return fail(LBM_E_INVAL, "NULL output");
     const size_t n = (size_t)tiles->n_tiles;
     out->state_bytes = lattice_elems(tiles, params->storage) * storage_size(params->storage);
-    out->table_bytes = TableLayout((int64_t)n).total;
+    out->table_bytes = TableLayout((int64_t)n, grid_tiles(tiles->nx, tiles->ny, tiles->nz)).total;
     out->scratch_bytes = (n + 1) * NSUM * sizeof(double);
     const size_t fe = field_entries(tiles);
     out->force_bytes = fe * arith_size(params->storage);
@@ -329,7 +329,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     // device current; a failure is reported by that entry point only
     c->noalloc_err = c->device >= 0 ? noalloc_lookup(c->device, &c->noalloc) : hipErrorNoDevice;
 
-    const TableLayout lay(n);
+    const TableLayout lay(n, grid_tiles(tiles->nx, tiles->ny, tiles->nz));
     if (n > 0) try {
         // device tile d holds discovery tile perm[d]; neighbour numbers are
         // translated with the inverse permutation
@@ -344,6 +344,9 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
         uint64_t *nbb64 = reinterpret_cast<uint64_t *>(host.data() + lay.nbb64_off);
         int32_t *xyz = reinterpret_cast<int32_t *>(host.data() + lay.xyz_off);
         uint64_t *fbase = reinterpret_cast<uint64_t *>(host.data() + lay.fld_off);
+        int32_t *map = reinterpret_cast<int32_t *>(host.data() + lay.map_off);
+        const int64_t gtx = ((int64_t)c->nx + 3) / 4, gty = ((int64_t)c->ny + 3) / 4;
+        std::fill(map, map + grid_tiles(c->nx, c->ny, c->nz), -1);
         uint64_t next = 0, next_field = 0;
         for (int64_t d = 0; d < n; ++d) {
             const int64_t i = perm[d];
@@ -359,6 +362,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
             for (int a = 0; a < 3; ++a) xyz[4 * d + a] = tiles->tile_xyz[3 * i + a];
             for (int a = 0; a < 3; ++a) c->corner[3 * d + a] = tiles->tile_xyz[3 * i + a];
             xyz[4 * d + 3] = 0;
+            map[xyz[4 * d] / 4 + gtx * (xyz[4 * d + 1] / 4 + gty * (int64_t)(xyz[4 * d + 2] / 4))] = (int32_t)d;
         }
         // neighbourhood rows (needs every tile's record first)
         for (int64_t d = 0; d < n; ++d) {
@@ -395,6 +399,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     c->L.tb.nbb64 = reinterpret_cast<const uint64_t *>(tb + lay.nbb64_off);
     c->L.tb.xyz = reinterpret_cast<const int32_t *>(tb + lay.xyz_off);
     c->L.tb.fbase = reinterpret_cast<const uint64_t *>(tb + lay.fld_off);
+    c->L.tb.map = reinterpret_cast<const int32_t *>(tb + lay.map_off);
     // every byte offset into a lattice (an adjoint lattice has the layout and
     // size of the state) must fit 32 bits for the 32-bit kernels
     c->L.off32 = c->state_bytes <= (size_t)UINT32_MAX && !c->params.wide_offsets;
@@ -639,16 +644,17 @@ static int macroscopic_into(lbm_ctx *c, const void *state, double *rho_dev, doub
     if (!state) state = cur_state(c);
     const size_t N = (size_t)c->nx * c->ny * c->nz;
     hipError_t e = hipSuccess;
-    if (rho_dev) e = launch_fill(c->stream, rho_dev, N);
-    if (e == hipSuccess && u_dev) e = launch_fill(c->stream, u_dev, 3 * N);
     double *final_ = partials + (size_t)c->n_tiles * NSUM;
     if (c->n_tiles == 0) {
+        if (rho_dev) e = launch_fill(c->stream, rho_dev, N);
+        if (e == hipSuccess && u_dev) e = launch_fill(c->stream, u_dev, 3 * N);
         for (int k = 0; k < NSUM; ++k) sums[k] = 0.0;
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         return launched(e, "lbm_macroscopic");
     }
-    if (e == hipSuccess) e = launch_macro(c->L, c->P, state, rho_dev, u_dev, c->nx, c->ny, c->nz, partials);
-    if (e == hipSuccess) e = launch_reduce(c->stream, partials, c->n_tiles, final_);
+    int rows = 0;
+    e = launch_macro(c->L, c->P, state, rho_dev, u_dev, c->nx, c->ny, c->nz, partials, &rows);
+    if (e == hipSuccess) e = launch_reduce(c->stream, partials, rows, final_);
     if (e == hipSuccess) e = hipMemcpyAsync(sums, final_, NSUM * sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(e, "lbm_macroscopic");
@@ -695,10 +701,7 @@ extern "C" int lbm_get_state(lbm_ctx *c, const void *state, double *f_dense_dev)
     CHECK_CTX(c);
     if (!f_dense_dev) return fail(LBM_E_INVAL, "lbm_get_state: NULL output");
     if (!state) state = cur_state(c);
-    const size_t N = (size_t)c->nx * c->ny * c->nz;
-    hipError_t e = launch_fill(c->stream, f_dense_dev, Q * N);
-    if (e == hipSuccess) e = launch_get_state(c->L, c->P, state, f_dense_dev, c->nx, c->ny, c->nz);
-    return launched(e, "lbm_get_state");
+    return launched(launch_get_state(c->L, c->P, state, f_dense_dev, c->nx, c->ny, c->nz), "lbm_get_state");
 }
 
 extern "C" int lbm_set_state(lbm_ctx *c, const double *f_dense_dev, void *state) {
@@ -713,20 +716,16 @@ extern "C" int lbm_tiles_to_dense(lbm_ctx *c, const void *tile_buf, int32_t ncom
     if (!tile_buf || !dense_dev) return fail(LBM_E_INVAL, "lbm_tiles_to_dense: NULL buffer");
     if (ncomp <= 0 || ncomp > 64) return fail(LBM_E_INVAL, "lbm_tiles_to_dense: ncomp must be in 1..64");
     if (dtype != 0 && dtype != 1) return fail(LBM_E_INVAL, "lbm_tiles_to_dense: dtype must be 0 (f64) or 1 (f32)");
-    const size_t N = (size_t)c->nx * c->ny * c->nz;
-    hipError_t e = launch_fill(c->stream, dense_dev, (size_t)ncomp * N);
-    if (e == hipSuccess) e = launch_tiles_to_dense(c->L, tile_buf, ncomp, dtype, dense_dev, c->nx, c->ny, c->nz);
-    return launched(e, "lbm_tiles_to_dense");
+    return launched(launch_tiles_to_dense(c->L, tile_buf, ncomp, dtype, dense_dev, c->nx, c->ny, c->nz),
+                    "lbm_tiles_to_dense");
 }
 
 extern "C" int lbm_field_to_dense(lbm_ctx *c, const void *field_buf, int32_t dtype, double *dense_dev) {
     CHECK_CTX(c);
     if (!dense_dev || (!field_buf && c->n_tiles > 0)) return fail(LBM_E_INVAL, "lbm_field_to_dense: NULL buffer");
     if (dtype != 0 && dtype != 1) return fail(LBM_E_INVAL, "lbm_field_to_dense: dtype must be 0 (f64) or 1 (f32)");
-    const size_t N = (size_t)c->nx * c->ny * c->nz;
-    hipError_t e = launch_fill(c->stream, dense_dev, 3 * N);
-    if (e == hipSuccess) e = launch_field_to_dense(c->L, field_buf, dtype, dense_dev, c->nx, c->ny, c->nz);
-    return launched(e, "lbm_field_to_dense");
+    return launched(launch_field_to_dense(c->L, field_buf, dtype, dense_dev, c->nx, c->ny, c->nz),
+                    "lbm_field_to_dense");
 }
 
 static int adjoint_supported(lbm_ctx *c) {
@@ -747,10 +746,7 @@ extern "C" int lbm_adjoint_get(lbm_ctx *c, const void *adj, double *dense_dev) {
     int rc = adjoint_supported(c);
     if (rc) return rc;
     if (!dense_dev || (!adj && c->n_tiles > 0)) return fail(LBM_E_INVAL, "lbm_adjoint_get: NULL buffer");
-    const size_t N = (size_t)c->nx * c->ny * c->nz;
-    hipError_t e = launch_fill(c->stream, dense_dev, Q * N);
-    if (e == hipSuccess) e = launch_get_state(c->L, unshifted(c), adj, dense_dev, c->nx, c->ny, c->nz);
-    return launched(e, "lbm_adjoint_get");
+    return launched(launch_get_state(c->L, unshifted(c), adj, dense_dev, c->nx, c->ny, c->nz), "lbm_adjoint_get");
 }
 
 extern "C" int lbm_adjoint_set(lbm_ctx *c, const double *dense_dev, void *adj) {

@@ -152,6 +152,8 @@ inline uint64_t run_elems(uint64_t mask, int storage) {
 //   [nbb64_off]  uint64 [n_tiles][20]: the 19 element offsets in 64 bits
 //   [xyz_off]    int32  [n_tiles][4]: corner x, y, z, 0
 //   [fld_off]    uint64 [n_tiles]: entry offset of the tile's per-node field run
+//   [map_off]    int32  [tz][ty][tx]: device tile number of each tile of the
+//                box, -1 for a dropped one (kernels that walk a dense array)
 // The neighbourhood is gathered once on the host, so a wave reads it with a
 // few wide scalar loads instead of chasing 19 tile numbers.  Everything a step
 // needs to know about a tile is in its row: one round trip to memory, where a
@@ -189,15 +191,17 @@ struct alignas(64) NbRow {
 static_assert(sizeof(NbRow) == 256, "a row is two whole 128-byte lines");
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct TableLayout {
-    size_t rec_off, row_off, nbb64_off, xyz_off, fld_off, total;
-    explicit TableLayout(int64_t n_tiles) {
+    size_t rec_off, row_off, nbb64_off, xyz_off, fld_off, map_off, total;
+    // n_grid: tiles of the whole box, kept or not
+    TableLayout(int64_t n_tiles, int64_t n_grid) {
         const size_t n = (size_t)n_tiles;
         rec_off = 0;
         row_off = align_up(rec_off + n * sizeof(TileRec), 256);
         nbb64_off = align_up(row_off + n * sizeof(NbRow), 256);
         xyz_off = align_up(nbb64_off + n * NB_STRIDE * 8, 256);
         fld_off = align_up(xyz_off + n * 16, 256);
-        total = align_up(fld_off + n * 8, 256);
+        map_off = align_up(fld_off + n * 8, 256);
+        total = n ? align_up(map_off + (size_t)n_grid * 4, 256) : 0;
     }
 };
 
@@ -207,9 +211,13 @@ struct DevTables {
     const uint64_t *nbb64;
     const int32_t *xyz;
     const uint64_t *fbase;
+    const int32_t *map;
 };
+inline int64_t grid_tiles(int32_t nx, int32_t ny, int32_t nz) {
+    return (((int64_t)nx + 3) / 4) * (((int64_t)ny + 3) / 4) * (((int64_t)nz + 3) / 4);
+}
 
-// reduction scratch: per-tile partials of 8 doubles + the final 8
+// reduction scratch: rows of 8 doubles, at most one row per tile + the final 8
 constexpr int NSUM = 8;
 
 }  // namespace tlbm

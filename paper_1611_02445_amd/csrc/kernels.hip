@@ -27,6 +27,7 @@
 // halfway bounce-back value at the node itself.
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <type_traits>
 #include <utility>
 
@@ -1015,13 +1016,17 @@ __global__ __launch_bounds__(512) void k_step_open(const NbRow *row, const uint6
 // kind 2 "propagation only"
 template <typename S, bool RN, int KIND, typename OffT>
 __global__ __launch_bounds__(512) void k_calib(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst, int n_tiles,
-                                               int lw, int nblocks) {
+                                               int lw, int nblocks, const TileRec *rec) {
     const int t = wave_tile<!RN>(lw, nblocks);
     if (t >= n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
-    const RowRegs r(row, t);
     Nbhd<OffT> h;
-    load_nbhd(h, r, nbb64, t);
+    if constexpr (KIND == 1) {  // no neighbours: the tile's record alone
+        h.m[OWN] = rec[t].mask;
+        h.base[OWN] = (OffT)rec[t].base;
+    } else {
+        load_nbhd(h, RowRegs(row, t), nbb64, t);
+    }
     const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
     const Self<RN, OffT> me(h, lane);
@@ -1167,122 +1172,275 @@ __device__ __forceinline__ double wave_max(double v) {
 }
 
 // ---------------------------------------------------------------------------
-// macroscopic fields of a stored post-collision lattice + per-tile FP64
-// partial sums: rho = sum f*, u = (sum c f* - F/2)/rho
+// a dense box, walked by rows of 16 nodes along x
 // ---------------------------------------------------------------------------
-template <int ST>
-__global__ __launch_bounds__(512) void k_macro(KArgs a, double *rho_out, double *u_out, int nx, int ny, int nz,
-                                              double *partials) {
-    using C = Codec<ST>;
-    using S = typename C::S;
-    using T = typename C::T;
-    const int t = wave_tile(a.lw, a.nblocks);
-    if (t >= a.n_tiles) return;
-    const int lane = (int)(threadIdx.x & 63);
-    const TileRec rec = a.tb.rec[t];
-    const bool fl = (rec.mask >> lane) & 1;
-    const Self<C::RUNS, uint64_t> me(rec, lane);
-    double drho = 0, jx = 0, jy = 0, jz = 0;
-    if (fl) {
+// One workgroup of 4 waves takes 4 tiles side by side along x, wave w their
+// z-plane w: lane l is node (l & 15, l >> 4) of the 16 x 4 nodes of that plane,
+// in tile l >> 2 & 3.  A store of a dense FP64 array is then 4 whole 128-byte
+// lines (a wave on its own tile writes 16 pieces of 32 bytes), the nodes of
+// tiles that were dropped are written too, so no pass over the array clears it
+// first, and a read of a lattice block is the 16 consecutive slots of each of
+// the 4 tiles' planes.
+struct DenseBox {
+    const int32_t *map;  // [tz][ty][tx] device tile number, -1 for a dropped tile
+    int tx, ty, gx;      // tiles along x and y, workgroups along x
+    int nx, ny, nz;
+};
+
+struct DenseNode {
+    bool in, fl;    // inside the box; a fluid node of a kept tile
+    int tile;       // device tile number, or -1
+    int n;          // node in the tile
+    int rank, k;    // the node's rank among the tile's k fluid nodes
+    uint64_t base;  // element offset of the tile's data
+    size_t at;      // index in a dense array
+    template <bool RUNS>
+    __device__ __forceinline__ uint64_t elem(int i) const {
+        return base + (uint64_t)(RUNS ? i * k + rank : i * TILE + n);
+    }
+    __device__ __forceinline__ uint64_t field_entry(uint64_t first, int c) const {
+        return first + (uint64_t)(c * k + rank);
+    }
+};
+
+// The groups of 4 tiles blockIdx.x, blockIdx.x + gridDim.x, ...  A node's
+// loads need its tile's record and that the tile's number: both are loaded
+// ahead, the record one group and the number two, so a group waits for its
+// lattice loads alone.
+// Each XCD takes chunks of 16 groups, 256 nodes along x, so that it writes
+// whole rows (256^3 pack, fields and sums: 378 us a call, 382 without the
+// re-numbering, 387 with chunks of 64).
+constexpr int DENSE_LC = 4;
+struct DenseWalk {
+    const DevTables &tb;
+    const DenseBox &b;
+    const int groups;
+    int g, tile1;
+    int tile0;
+    TileRec rec0;
+    __device__ __forceinline__ DenseWalk(const DevTables &tb_, const DenseBox &b_, int groups_)
+        : tb(tb_), b(b_), groups(groups_), g((int)blockIdx.x) {
+        tile0 = lookup(g);
+        tile1 = lookup(g + (int)gridDim.x);
+        rec0 = record(tile0);
+    }
+    __device__ __forceinline__ bool more() const { return g < groups; }
+    __device__ __forceinline__ int lookup(int i) const {
+        if (i >= groups) return -1;
+        const int gr = remap_block(i, groups, DENSE_LC);
+        const int row = gr / b.gx, tx = 4 * (gr - row * b.gx) + (int)(threadIdx.x >> 2 & 3);
+        return tx < b.tx ? b.map[(size_t)row * b.tx + tx] : -1;
+    }
+    __device__ __forceinline__ TileRec record(int t) const { return t >= 0 ? tb.rec[t] : TileRec{0, 0}; }
+    // the node of this thread in the present group; moves on to the next one
+    __device__ __forceinline__ DenseNode next() {
+        DenseNode d;
+        const int lane = (int)(threadIdx.x & 63), z = (int)(threadIdx.x >> 6);
+        const int gr = remap_block(g, groups, DENSE_LC);
+        const int row = gr / b.gx, gx = gr - row * b.gx;
+        const int tz = row / b.ty, ty = row - tz * b.ty;
+        const int x16 = lane & 15, y = lane >> 4;
+        const int X = 16 * gx + x16, Y = 4 * ty + y, Z = 4 * tz + z;
+        d.in = X < b.nx && Y < b.ny && Z < b.nz;
+        d.at = (size_t)X + (size_t)b.nx * ((size_t)Y + (size_t)b.ny * (size_t)Z);
+        d.n = (x16 & 3) + 4 * y + 16 * z;
+        d.tile = tile0;
+        d.base = rec0.base;
+        d.fl = (rec0.mask >> d.n) & 1;
+        d.k = __builtin_popcountll(rec0.mask);
+        d.rank = __builtin_popcountll(rec0.mask & ((1ull << d.n) - 1ull));
+        tile0 = tile1;
+        rec0 = record(tile1);
+        tile1 = lookup(g + 2 * (int)gridDim.x);
+        g += (int)gridDim.x;
+        return d;
+    }
+};
+
+// ---------------------------------------------------------------------------
+// macroscopic fields of a stored post-collision lattice and their sums:
+// rho = sum f*, u = (sum c f* - F/2)/rho
+// ---------------------------------------------------------------------------
+// A lane keeps the 8 sums of the nodes it visits and its workgroup reduces
+// them once at the end: a butterfly per tile (96 cross-lane moves, through the
+// LDS pipe) took longer than reading the tile.  Every workgroup leaves one row
+// of partial sums; the work and the order of every addition follow from the
+// launch shape alone, so the sums are bitwise reproducible.
+struct MacroSums {
+    double v[NSUM];
+    __device__ __forceinline__ MacroSums() {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const double v = (double)C::dec(load_elem<uint64_t, S>(a.src, me.elem(i)), a.P.inv_scale);
-            drho += v;
-            jx += CX[i] * v;
-            jy += CY[i] * v;
-            jz += CZ[i] * v;
-        }
+        for (int c = 0; c < NSUM; ++c) v[c] = 0.0;
     }
-    T Fx = T(0), Fy = T(0), Fz = T(0);
-    if (fl) load_force<T>(a.P, a.P.field ? a.tb.fbase[t] : 0, rec.mask, Fx, Fy, Fz);
-    const double rho = a.P.rho_base + drho;
-    const double mx = jx - 0.5 * (double)Fx, my = jy - 0.5 * (double)Fy, mz = jz - 0.5 * (double)Fz;
-    double ux = mx, uy = my, uz = mz;
-    if (!(a.P.model & 1)) {  // quasi-compressible velocity (either operator)
-        ux = mx / rho;
-        uy = my / rho;
-        uz = mz / rho;
+    __device__ __forceinline__ void add(double rho, double ux, double uy, double uz) {
+        const bool finite = isfinite(rho) && isfinite(ux) && isfinite(uy) && isfinite(uz);
+        v[0] += rho;
+        v[1] += rho * ux;
+        v[2] += rho * uy;
+        v[3] += rho * uz;
+        v[4] += 1.0;
+        if (finite) v[5] = fmax(v[5], sqrt(ux * ux + uy * uy + uz * uz));
+        else v[6] += 1.0;
+        v[7] += ux;
     }
-    if (fl) {
-        const size_t N = (size_t)nx * ny * nz;
-        const size_t n = dense_index(a.tb.xyz + 4 * (size_t)t, lane, nx, ny);
-        if (rho_out) rho_out[n] = rho;
-        if (u_out) {
-            u_out[n] = ux;
-            u_out[N + n] = uy;
-            u_out[2 * N + n] = uz;
-        }
+    // by all threads of a workgroup of MACRO_THREADS, into its row of partials
+    __device__ __forceinline__ void store(double *partials);
+};
+constexpr int MACRO_THREADS = 256;
+__device__ __forceinline__ void MacroSums::store(double *partials) {
+    __shared__ double sh[MACRO_THREADS / 64][NSUM];
+    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+#pragma unroll
+    for (int c = 0; c < NSUM; ++c) {
+        const double r = c == 5 ? wave_max(v[c]) : wave_sum(v[c]);
+        if (lane == 0) sh[wave][c] = r;
     }
-    const bool finite = isfinite(rho) && isfinite(ux) && isfinite(uy) && isfinite(uz);
-    const double s0 = wave_sum(fl ? rho : 0.0);
-    const double s1 = wave_sum(fl ? rho * ux : 0.0);
-    const double s2 = wave_sum(fl ? rho * uy : 0.0);
-    const double s3 = wave_sum(fl ? rho * uz : 0.0);
-    const double s4 = wave_sum(fl ? 1.0 : 0.0);
-    const double s5 = wave_max(fl && finite ? sqrt(ux * ux + uy * uy + uz * uz) : 0.0);
-    const double s6 = wave_sum(fl && !finite ? 1.0 : 0.0);
-    const double s7 = wave_sum(fl ? ux : 0.0);
-    if (lane == 0) {
-        double *p = partials + (size_t)t * NSUM;
-        p[0] = s0;
-        p[1] = s1;
-        p[2] = s2;
-        p[3] = s3;
-        p[4] = s4;
-        p[5] = s5;
-        p[6] = s6;
-        p[7] = s7;
+    __syncthreads();
+    if (threadIdx.x < NSUM) {
+        const int c = (int)threadIdx.x;
+        double r = sh[0][c];
+        for (int w = 1; w < MACRO_THREADS / 64; ++w) r = c == 5 ? fmax(r, sh[w][c]) : r + sh[w][c];
+        partials[(size_t)blockIdx.x * NSUM + c] = r;
     }
 }
 
-// one workgroup reduces the per-tile partials in a fixed order
-constexpr int RED_THREADS = 512;
-__global__ __launch_bounds__(RED_THREADS) void k_reduce(const double *partials, int n_tiles, double *out) {
-    __shared__ double sh[NSUM][RED_THREADS];
-    const int tid = (int)threadIdx.x;
-    double acc[NSUM];
+// rho and the velocity of one fluid node; load(i) is its stored value i
+template <class Load>
+__device__ __forceinline__ void macro_node(const Phys &P, double Fx, double Fy, double Fz, Load load, double &rho,
+                                           double &ux, double &uy, double &uz) {
+    double drho = 0, jx = 0, jy = 0, jz = 0;
 #pragma unroll
-    for (int c = 0; c < NSUM; ++c) acc[c] = 0.0;
-    for (int j = tid; j < n_tiles; j += RED_THREADS) {
+    for (int i = 0; i < Q; ++i) {
+        const double v = load(i);
+        drho += v;
+        jx += CX[i] * v;
+        jy += CY[i] * v;
+        jz += CZ[i] * v;
+    }
+    rho = P.rho_base + drho;
+    ux = jx - 0.5 * Fx;
+    uy = jy - 0.5 * Fy;
+    uz = jz - 0.5 * Fz;
+    if (!(P.model & 1)) {  // quasi-compressible velocity (either operator)
+        ux = ux / rho;
+        uy = uy / rho;
+        uz = uz / rho;
+    }
+}
+
+// the sums alone, tile after tile: no dropped tile is visited
+template <int ST>
+__global__ __launch_bounds__(MACRO_THREADS) void k_sums(KArgs a, double *partials) {
+    using C = Codec<ST>;
+    using S = typename C::S;
+    using T = typename C::T;
+    const int lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int waves = (int)gridDim.x * (MACRO_THREADS / 64);
+    MacroSums sums;
+    int t = (int)blockIdx.x * (MACRO_THREADS / 64) + wave;
+    TileRec ahead = t < a.n_tiles ? a.tb.rec[t] : TileRec{0, 0};
+    for (; t < a.n_tiles; t += waves) {
+        const TileRec rec = ahead;
+        ahead = t + waves < a.n_tiles ? a.tb.rec[t + waves] : TileRec{0, 0};
+        if (!((rec.mask >> lane) & 1)) continue;
+        const Self<C::RUNS, uint64_t> me(rec, lane);
+        S raw[Q];
 #pragma unroll
-        for (int c = 0; c < NSUM; ++c) {
-            const double v = partials[(size_t)j * NSUM + c];
-            acc[c] = (c == 5) ? fmax(acc[c], v) : acc[c] + v;
+        for (int i = 0; i < Q; ++i) raw[i] = load_elem<uint64_t, S>(a.src, me.elem(i));
+        T Fx, Fy, Fz;
+        load_force<T>(a.P, a.P.field ? a.tb.fbase[t] : 0, rec.mask, Fx, Fy, Fz);
+        double rho, ux, uy, uz;
+        macro_node(a.P, (double)Fx, (double)Fy, (double)Fz,
+                   [&](int i) { return (double)C::dec(raw[i], a.P.inv_scale); }, rho, ux, uy, uz);
+        sums.add(rho, ux, uy, uz);
+    }
+    sums.store(partials);
+}
+
+// the fields, and with SUMS the sums of the same pass
+template <int ST, bool SUMS>
+__global__ __launch_bounds__(MACRO_THREADS) void k_fields(KArgs a, DenseBox b, int groups, double *rho_out,
+                                                          double *u_out, double *partials) {
+    using C = Codec<ST>;
+    using S = typename C::S;
+    using T = typename C::T;
+    const size_t N = (size_t)b.nx * b.ny * b.nz;
+    MacroSums sums;
+    for (DenseWalk w(a.tb, b, groups); w.more();) {
+        const DenseNode d = w.next();
+        double rho = 0, ux = 0, uy = 0, uz = 0;
+        if (d.fl) {
+            S raw[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) raw[i] = load_elem<uint64_t, S>(a.src, d.template elem<C::RUNS>(i));
+            T Fx = T(a.P.F[0]), Fy = T(a.P.F[1]), Fz = T(a.P.F[2]);
+            if (a.P.field) {
+                const T *f = reinterpret_cast<const T *>(a.P.field);
+                const uint64_t first = a.tb.fbase[d.tile];
+                Fx = f[d.field_entry(first, 0)];
+                Fy = f[d.field_entry(first, 1)];
+                Fz = f[d.field_entry(first, 2)];
+            }
+            macro_node(a.P, (double)Fx, (double)Fy, (double)Fz,
+                       [&](int i) { return (double)C::dec(raw[i], a.P.inv_scale); }, rho, ux, uy, uz);
+            if constexpr (SUMS) sums.add(rho, ux, uy, uz);
+        }
+        if (d.in) {
+            if (rho_out) rho_out[d.at] = rho;
+            if (u_out) {
+                u_out[d.at] = ux;
+                u_out[N + d.at] = uy;
+                u_out[2 * N + d.at] = uz;
+            }
         }
     }
-#pragma unroll
-    for (int c = 0; c < NSUM; ++c) sh[c][tid] = acc[c];
+    if constexpr (SUMS) sums.store(partials);
+}
+
+// one workgroup reduces the rows of partial sums in a fixed order: thread t
+// takes column t % 8 of every 64th row, then the 64 threads of a column meet
+// in LDS
+constexpr int RED_THREADS = 64 * NSUM;
+__global__ __launch_bounds__(RED_THREADS) void k_reduce(const double *partials, int rows, double *out) {
+    __shared__ double sh[RED_THREADS];
+    const int tid = (int)threadIdx.x, c = tid % NSUM;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int j = tid; j < rows * NSUM; j += RED_THREADS) {
+        const double v = partials[j];
+        acc = (c == 5) ? fmax(acc, v) : acc + v;
+    }
+    sh[tid] = acc;
     __syncthreads();
-    for (int s = RED_THREADS / 2; s > 0; s >>= 1) {
-        if (tid < s) {
-#pragma unroll
-            for (int c = 0; c < NSUM; ++c)
-                sh[c][tid] = (c == 5) ? fmax(sh[c][tid], sh[c][tid + s]) : sh[c][tid] + sh[c][tid + s];
-        }
+    for (int s = RED_THREADS / 2; s >= NSUM; s >>= 1) {
+        if (tid < s) sh[tid] = (c == 5) ? fmax(sh[tid], sh[tid + s]) : sh[tid] + sh[tid + s];
         __syncthreads();
     }
-    if (tid < NSUM) out[tid] = sh[tid][0];
+    if (tid < NSUM) out[tid] = sh[tid];
 }
 
 // ---------------------------------------------------------------------------
 // dense <-> tile conversions
 // ---------------------------------------------------------------------------
 template <int ST>
-__global__ __launch_bounds__(512) void k_get_state(KArgs a, double *dense, int nx, int ny, int nz) {
+__global__ __launch_bounds__(256) void k_get_state(KArgs a, DenseBox b, int groups, double *dense) {
     using C = Codec<ST>;
     using S = typename C::S;
-    const int t = wave_tile(a.lw, a.nblocks);
-    if (t >= a.n_tiles) return;
-    const int lane = (int)(threadIdx.x & 63);
-    const TileRec rec = a.tb.rec[t];
-    if (!((rec.mask >> lane) & 1)) return;  // the dense array was zero-filled
-    const Self<C::RUNS, uint64_t> me(rec, lane);
-    const size_t N = (size_t)nx * ny * nz;
-    const size_t n = dense_index(a.tb.xyz + 4 * (size_t)t, lane, nx, ny);
+    const size_t N = (size_t)b.nx * b.ny * b.nz;
+    for (DenseWalk w(a.tb, b, groups); w.more();) {
+        const DenseNode d = w.next();
+        S raw[Q];
+        if (d.fl) {
 #pragma unroll
-    for (int i = 0; i < Q; ++i)
-        dense[(size_t)i * N + n] =
-            (double)C::dec(load_elem<uint64_t, S>(a.src, me.elem(i)), a.P.inv_scale) + weight(i) * a.P.rho_base;
+            for (int i = 0; i < Q; ++i) raw[i] = load_elem<uint64_t, S>(a.src, d.template elem<C::RUNS>(i));
+        }
+        if (!d.in) continue;
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            dense[(size_t)i * N + d.at] =
+                d.fl ? (double)C::dec(raw[i], a.P.inv_scale) + weight(i) * a.P.rho_base : 0.0;
+    }
 }
 
 template <int ST>
@@ -1298,9 +1456,14 @@ __global__ __launch_bounds__(512) void k_set_state(KArgs a, const double *dense,
     const Self<C::RUNS, uint64_t> me(rec, lane);
     const size_t N = (size_t)nx * ny * nz;
     const size_t n = dense_index(a.tb.xyz + 4 * (size_t)t, lane, nx, ny);
-    auto value = [&](int i) {
-        return C::enc((T)(dense[(size_t)i * N + n] - weight(i) * a.P.rho_base), a.P.scale);
-    };
+    // every load before the first store (the compiler has to take it that a
+    // store may change the dense array)
+    double v[Q];
+    if (fl) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) v[i] = dense[(size_t)i * N + n];
+    }
+    auto value = [&](int i) { return C::enc((T)(v[i] - weight(i) * a.P.rho_base), a.P.scale); };
     if constexpr (C::RUNS) {
         store_tile<S, true, uint64_t, false>(a.dst, me, rec.mask, fl, lane, value);
     } else {
@@ -1331,29 +1494,31 @@ __global__ __launch_bounds__(512) void k_force_to_tiles(KArgs a, const double *g
 
 // per-fluid-slot field [3 components] -> dense FP64 [3][nz][ny][nx]
 template <typename T>
-__global__ __launch_bounds__(512) void k_field_to_dense(KArgs a, const T *in, double *dense, int nx, int ny, int nz) {
-    const int t = wave_tile(a.lw, a.nblocks);
-    if (t >= a.n_tiles) return;
-    const int lane = (int)(threadIdx.x & 63);
-    const uint64_t mask = a.tb.rec[t].mask;
-    if (!((mask >> lane) & 1)) return;  // the dense array was zero-filled
-    const FieldSlot fs(a.tb, t, mask);
-    const size_t N = (size_t)nx * ny * nz;
-    const size_t n = dense_index(a.tb.xyz + 4 * (size_t)t, lane, nx, ny);
+__global__ __launch_bounds__(256) void k_field_to_dense(KArgs a, DenseBox b, int groups, const T *in, double *dense) {
+    const size_t N = (size_t)b.nx * b.ny * b.nz;
+    for (DenseWalk w(a.tb, b, groups); w.more();) {
+        const DenseNode d = w.next();
+        T v[3] = {T(0), T(0), T(0)};
+        if (d.fl) {
+            const uint64_t first = a.tb.fbase[d.tile];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) dense[(size_t)c * N + n] = (double)in[fs.entry(c)];
+            for (int c = 0; c < 3; ++c) v[c] = in[d.field_entry(first, c)];
+        }
+        if (!d.in) continue;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dense[(size_t)c * N + d.at] = (double)v[c];
+    }
 }
 
 template <typename T>
-__global__ __launch_bounds__(512) void k_tiles_to_dense(KArgs a, const T *in, int ncomp, double *dense, int nx, int ny,
-                                                       int nz) {
-    const int t = wave_tile(a.lw, a.nblocks);
-    if (t >= a.n_tiles) return;
-    const int lane = (int)(threadIdx.x & 63);
-    const bool fl = (a.tb.rec[t].mask >> lane) & 1;
-    const size_t N = (size_t)nx * ny * nz;
-    const size_t n = dense_index(a.tb.xyz + 4 * (size_t)t, lane, nx, ny);
-    for (int c = 0; c < ncomp; ++c) dense[(size_t)c * N + n] = fl ? (double)in[((size_t)t * ncomp + c) * TILE + lane] : 0.0;
+__global__ __launch_bounds__(256) void k_tiles_to_dense(KArgs a, DenseBox b, int groups, const T *in, int ncomp, double *dense) {
+    const size_t N = (size_t)b.nx * b.ny * b.nz;
+    for (DenseWalk w(a.tb, b, groups); w.more();) {
+        const DenseNode d = w.next();
+        if (!d.in) continue;
+        for (int c = 0; c < ncomp; ++c)
+            dense[(size_t)c * N + d.at] = d.fl ? (double)in[((size_t)d.tile * ncomp + c) * TILE + d.n] : 0.0;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1804,9 +1969,11 @@ template <int ST, int KIND>
 static hipError_t calib_t(const Launch &L, const KArgs &a) {
     using C = Codec<ST>;
     if (L.off32)
-        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint32_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a));
+        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint32_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a),
+                           a.tb.rec);
     else
-        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint64_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a));
+        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint64_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a),
+                           a.tb.rec);
     return hipGetLastError();
 }
 
@@ -1868,32 +2035,104 @@ hipError_t launch_fill(hipStream_t s, double *p, size_t n) {
     return hipGetLastError();
 }
 
-hipError_t launch_macro(const Launch &L, const Phys &P, const void *state, double *rho, double *u, int nx, int ny,
-                        int nz, double *partials) {
-    if (L.n_tiles == 0) return hipSuccess;
-    const KArgs a = make_args(L, P, state, nullptr);
-    switch (P.storage) {
-    case LBM_F64: hipLaunchKernelGGL(k_macro<LBM_F64>, dim3(L.grid), block_of(L), 0, L.stream, a, rho, u, nx, ny, nz, partials); break;
-    case LBM_F32: hipLaunchKernelGGL(k_macro<LBM_F32>, dim3(L.grid), block_of(L), 0, L.stream, a, rho, u, nx, ny, nz, partials); break;
-    default: hipLaunchKernelGGL(k_macro<LBM_F16S>, dim3(L.grid), block_of(L), 0, L.stream, a, rho, u, nx, ny, nz, partials); break;
+static DenseBox dense_box(const Launch &L, int nx, int ny, int nz) {
+    DenseBox b;
+    b.map = L.tb.map;
+    b.tx = (nx + 3) / 4;
+    b.ty = (ny + 3) / 4;
+    b.gx = (b.tx + 3) / 4;
+    b.nx = nx;
+    b.ny = ny;
+    b.nz = nz;
+    return b;
+}
+
+// workgroups of a dense walk, or -1 when they do not fit a grid (no such box
+// fits the memory)
+static int dense_groups(const DenseBox &b) {
+    const int64_t g = (int64_t)b.gx * b.ty * ((b.nz + 3) / 4);
+    return g <= INT32_MAX ? (int)g : -1;
+}
+
+// Workgroups of a pass that walks the tiles or the box in strides: all that
+// are resident at once (2048 of 4 waves, 8 waves per SIMD), and 4 times that
+// for the fields, whose walk gains from it (256^3 pack: 378 us a call against
+// 392 with 2048 and 470 with one workgroup per group).  A summing pass has at
+// most one workgroup per tile, for which there are rows of partial sums.
+constexpr int SUM_GROUPS = 2048;
+constexpr int FIELD_GROUPS = 8192;
+
+template <int ST>
+static hipError_t macro_t(const Launch &L, const KArgs &a, double *rho, double *u, int nx, int ny, int nz,
+                          double *partials, int *rows) {
+    const DenseBox b = dense_box(L, nx, ny, nz);
+    const int groups = dense_groups(b);
+    if (groups < 0) return hipErrorInvalidValue;
+    const bool fields = rho || u;
+    // with fewer tiles than that, a box may be large and nearly empty: its
+    // fields are written by a pass of their own, with a full launch
+    const bool fused = fields && L.n_tiles >= SUM_GROUPS;
+    if (fields) {
+        int grid = groups < FIELD_GROUPS ? groups : FIELD_GROUPS;
+        if (fused && grid > L.n_tiles) grid = L.n_tiles;
+        if (fused)
+            hipLaunchKernelGGL((k_fields<ST, true>), dim3(grid), dim3(MACRO_THREADS), 0, L.stream, a, b, groups, rho, u,
+                               partials);
+        else
+            hipLaunchKernelGGL((k_fields<ST, false>), dim3(grid), dim3(MACRO_THREADS), 0, L.stream, a, b, groups, rho,
+                               u, partials);
+        *rows = grid;
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || fused) return e;
     }
+    const int waves = MACRO_THREADS / 64, tiles = (L.n_tiles + waves - 1) / waves;
+    const int grid = tiles < SUM_GROUPS ? tiles : SUM_GROUPS;
+    hipLaunchKernelGGL(k_sums<ST>, dim3(grid), dim3(MACRO_THREADS), 0, L.stream, a, partials);
+    *rows = grid;
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(hipStream_t s, const double *partials, int n_tiles, double *out) {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(RED_THREADS), 0, s, partials, n_tiles, out);
+// rows: how many rows of partial sums launch_reduce is to add up (at most one
+// per tile)
+hipError_t launch_macro(const Launch &L, const Phys &P, const void *state, double *rho, double *u, int nx, int ny,
+                        int nz, double *partials, int *rows) {
+    *rows = 0;
+    if (L.n_tiles == 0) return hipSuccess;
+    const KArgs a = make_args(L, P, state, nullptr);
+    switch (P.storage) {
+    case LBM_F64: return macro_t<LBM_F64>(L, a, rho, u, nx, ny, nz, partials, rows);
+    case LBM_F32: return macro_t<LBM_F32>(L, a, rho, u, nx, ny, nz, partials, rows);
+    default: return macro_t<LBM_F16S>(L, a, rho, u, nx, ny, nz, partials, rows);
+    }
+}
+
+hipError_t launch_reduce(hipStream_t s, const double *partials, int rows, double *out) {
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(RED_THREADS), 0, s, partials, rows, out);
+    return hipGetLastError();
+}
+
+// runs a kernel of the dense walk, or clears `out` where no tile is kept (the
+// tables are then absent)
+template <class K, class... Args>
+static hipError_t dense_walk(const Launch &L, K kernel, const KArgs &a, int nx, int ny, int nz, size_t out_elems,
+                             double *out, Args... args) {
+    if (L.n_tiles == 0) return launch_fill(L.stream, out, out_elems);
+    const DenseBox b = dense_box(L, nx, ny, nz);
+    const int groups = dense_groups(b);
+    if (groups < 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kernel, dim3(groups < SUM_GROUPS ? groups : SUM_GROUPS), dim3(256), 0, L.stream, a, b, groups,
+                       args...);
     return hipGetLastError();
 }
 
 hipError_t launch_get_state(const Launch &L, const Phys &P, const void *state, double *dense, int nx, int ny, int nz) {
-    if (L.n_tiles == 0) return hipSuccess;
     const KArgs a = make_args(L, P, state, nullptr);
+    const size_t n = (size_t)Q * nx * ny * nz;
     switch (P.storage) {
-    case LBM_F64: hipLaunchKernelGGL(k_get_state<LBM_F64>, dim3(L.grid), block_of(L), 0, L.stream, a, dense, nx, ny, nz); break;
-    case LBM_F32: hipLaunchKernelGGL(k_get_state<LBM_F32>, dim3(L.grid), block_of(L), 0, L.stream, a, dense, nx, ny, nz); break;
-    default: hipLaunchKernelGGL(k_get_state<LBM_F16S>, dim3(L.grid), block_of(L), 0, L.stream, a, dense, nx, ny, nz); break;
+    case LBM_F64: return dense_walk(L, k_get_state<LBM_F64>, a, nx, ny, nz, n, dense, dense);
+    case LBM_F32: return dense_walk(L, k_get_state<LBM_F32>, a, nx, ny, nz, n, dense, dense);
+    default: return dense_walk(L, k_get_state<LBM_F16S>, a, nx, ny, nz, n, dense, dense);
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_set_state(const Launch &L, const Phys &P, const double *dense, void *state, int nx, int ny, int nz) {
@@ -1921,30 +2160,26 @@ hipError_t launch_force_to_tiles(const Launch &L, const Phys &P, const double *g
 
 hipError_t launch_field_to_dense(const Launch &L, const void *field, int dtype, double *dense, int nx, int ny,
                                  int nz) {
-    if (L.n_tiles == 0) return hipSuccess;
     Phys P{};
     const KArgs a = make_args(L, P, nullptr, nullptr);
+    const size_t n = (size_t)3 * nx * ny * nz;
     if (dtype == 0)
-        hipLaunchKernelGGL(k_field_to_dense<double>, dim3(L.grid), block_of(L), 0, L.stream, a,
-                           reinterpret_cast<const double *>(field), dense, nx, ny, nz);
-    else
-        hipLaunchKernelGGL(k_field_to_dense<float>, dim3(L.grid), block_of(L), 0, L.stream, a,
-                           reinterpret_cast<const float *>(field), dense, nx, ny, nz);
-    return hipGetLastError();
+        return dense_walk(L, k_field_to_dense<double>, a, nx, ny, nz, n, dense, reinterpret_cast<const double *>(field),
+                          dense);
+    return dense_walk(L, k_field_to_dense<float>, a, nx, ny, nz, n, dense, reinterpret_cast<const float *>(field),
+                      dense);
 }
 
 hipError_t launch_tiles_to_dense(const Launch &L, const void *tile_buf, int ncomp, int dtype, double *dense, int nx,
                                  int ny, int nz) {
-    if (L.n_tiles == 0) return hipSuccess;
     Phys P{};
     const KArgs a = make_args(L, P, nullptr, nullptr);
+    const size_t n = (size_t)ncomp * nx * ny * nz;
     if (dtype == 0)
-        hipLaunchKernelGGL(k_tiles_to_dense<double>, dim3(L.grid), block_of(L), 0, L.stream, a,
-                           reinterpret_cast<const double *>(tile_buf), ncomp, dense, nx, ny, nz);
-    else
-        hipLaunchKernelGGL(k_tiles_to_dense<float>, dim3(L.grid), block_of(L), 0, L.stream, a,
-                           reinterpret_cast<const float *>(tile_buf), ncomp, dense, nx, ny, nz);
-    return hipGetLastError();
+        return dense_walk(L, k_tiles_to_dense<double>, a, nx, ny, nz, n, dense,
+                          reinterpret_cast<const double *>(tile_buf), ncomp, dense);
+    return dense_walk(L, k_tiles_to_dense<float>, a, nx, ny, nz, n, dense, reinterpret_cast<const float *>(tile_buf),
+                      ncomp, dense);
 }
 
 // the adjoint kernels exist for FP64 and FP32 storage (runs layout) and every

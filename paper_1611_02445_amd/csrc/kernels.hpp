@@ -41,8 +41,8 @@ hipError_t launch_calib(const Launch &L, int kind, int storage, const void *src,
 hipError_t launch_init(const Launch &L, const Phys &P, void *a, void *b, double ux, double uy, double uz);
 hipError_t launch_fill(hipStream_t s, double *p, size_t n);
 hipError_t launch_macro(const Launch &L, const Phys &P, const void *state, double *rho, double *u, int nx, int ny,
-                        int nz, double *partials);
-hipError_t launch_reduce(hipStream_t s, const double *partials, int n_tiles, double *out);
+                        int nz, double *partials, int *rows);
+hipError_t launch_reduce(hipStream_t s, const double *partials, int rows, double *out);
 hipError_t launch_get_state(const Launch &L, const Phys &P, const void *state, double *dense, int nx, int ny, int nz);
 hipError_t launch_set_state(const Launch &L, const Phys &P, const double *dense, void *state, int nx, int ny, int nz);
 hipError_t launch_force_to_tiles(const Launch &L, const Phys &P, const double *g_dense, void *tile_buf, int nx,
