@@ -128,9 +128,24 @@ int no_throw(const char *what, F &&f) {
     }
 }
 
-// tiles (waves) per workgroup when the caller leaves it to the library: 4 was
-// the fastest of 1, 2, 4, 8 for every storage type on the sphere packs
+// Tiles (waves) per workgroup when the caller leaves it to the library.  4 is
+// the fastest of 1, 2, 4, 8 for every storage type on large grids (1 and 2
+// cost 1-4% from 100,000 tiles on).  A small grid has all its tiles in flight
+// at once and takes as long as the busiest CU, so fewer tiles per workgroup
+// are used where they spread it better: the workgroups go round the 256 CUs,
+// and 3300 tiles put 16 waves on some at four per workgroup, 13 at one (FP64
+// step 14.1 -> 13.0 us, adjoint 20.8 -> 19.6), 512 tiles 4 and 2 (6.5 -> 6.1
+// us); 4096 tiles come out even, and four is faster there (16.2 against 16.9 us).
 constexpr int DEFAULT_TPW = 4;
+constexpr int64_t CUS = 256;
+int default_tpw(int64_t n) {
+    const auto busiest = [n](int tpw) { return ((n + tpw - 1) / tpw + CUS - 1) / CUS * tpw; };
+    int best = DEFAULT_TPW;
+    for (int tpw = DEFAULT_TPW / 2; tpw >= 1; tpw /= 2)
+        // a gain of less than 10% is lost again in the sharing of lines
+        if (busiest(tpw) < busiest(best) && 10 * busiest(tpw) <= 9 * busiest(DEFAULT_TPW)) best = tpw;
+    return best;
+}
 // device tile order when the caller leaves it to the library: Morton (the
 // Hilbert order ties it, discovery order and the slabs trail)
 constexpr int DEFAULT_TILE_ORDER = 4;
@@ -309,7 +324,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     lbm_ctx *c = new (std::nothrow) lbm_ctx();
     if (!c) return fail(LBM_E_NOMEM, "lbm_create: out of host memory");
     c->params = *params;
-    if (c->params.tiles_per_wg == 0) c->params.tiles_per_wg = DEFAULT_TPW;
+    if (c->params.tiles_per_wg == 0) c->params.tiles_per_wg = default_tpw(n);
     if (c->params.tile_order == 0) c->params.tile_order = DEFAULT_TILE_ORDER;
     c->nx = tiles->nx;
     c->ny = tiles->ny;
