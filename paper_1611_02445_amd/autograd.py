@@ -265,7 +265,8 @@ class MeanVelocityLoss(torch.autograd.Function):
         run = CheckpointedAdjoint(lat, T, K, K2)
         loss = run.forward(f0.detach())
         ctx.run = run
-        return torch.tensor(loss, dtype=torch.float64, device=f0.device)
+        # a fill on the device: a copy from host memory would be waited for
+        return torch.full((), loss, dtype=torch.float64, device=f0.device)
 
     @staticmethod
     def backward(ctx, grad_out):
