@@ -530,6 +530,56 @@ __device__ __forceinline__ void store_tile(char *lattice, const Self<RUNS, OffT>
     }
 }
 
+// The same through LDS: a wave puts its tile's blocks side by side and writes
+// them 16 bytes per lane and store.  What a step is short of is the vector
+// memory path of its compute unit, which takes a cycle per 16 lanes and line
+// of an access and holds some 64 lines to come: a direction at a time a tile's
+// stores took about 95 cycles of it, this way 30 to 76 (256^3 pack, us a step:
+// FP64 388.5 -> 373.1, FP32 217.8 -> 202.5, FP16 159.0 -> 158.2; 128^3 dense
+// box FP16 35.3 -> 34.7; FP64 adjoint step on a 128^3 pack 100.5 -> 98.5).  The LDS round
+// trip is in every wave's way, though, and on a grid that is in flight all at
+// once nothing hides it: see stage_stores.
+// Same bytes as store_tile's.  For the plain layout value(i) is evaluated on
+// every lane and has to be zero on solid ones.
+template <typename S>
+constexpr int STAGE_BYTES = Q * TILE * (int)sizeof(S);  // of a wave
+extern __shared__ __align__(16) unsigned char stage_lds[];
+
+template <typename S, bool RUNS, typename OffT, class Value>
+__device__ __forceinline__ void store_tile_staged(char *lattice, const Self<RUNS, OffT> &me, bool fl, int lane,
+                                                  Value value) {
+    typedef uint32_t Chunk __attribute__((ext_vector_type(4)));
+    constexpr int L = 128 / (int)sizeof(S), MOST = (STAGE_BYTES<S> / 16 + 63) / 64;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    unsigned char *stage = stage_lds + wave * STAGE_BYTES<S>;
+    S *out = reinterpret_cast<S *>(stage);
+    int end = Q * TILE;  // values written
+    if constexpr (RUNS) {
+        if (fl) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) out[i * me.k + me.slot] = value(i);
+        }
+        const int used = Q * me.k;
+        end = (used + L - 1) / L * L;
+        if (lane < end - used) out[used + lane] = S(0);
+    } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) out[i * TILE + lane] = value(i);
+    }
+    // no other wave touches this one's part, and its own accesses are in order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int chunks = end * (int)sizeof(S) / 16;
+    Chunk *to = reinterpret_cast<Chunk *>(lattice + (size_t)me.base * sizeof(S));
+    const Chunk *from = reinterpret_cast<const Chunk *>(stage);
+#pragma unroll
+    for (int c = 0; c < MOST; ++c) {
+        if (c * 64 >= chunks) break;
+        const int e = c * 64 + lane;
+        if (e < chunks) __builtin_nontemporal_store(from[e], to + e);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // collision: LBGK (Eq. 2, 7) with the quasi-compressible (Eq. 3, 5) or
 // incompressible (Eq. 4, 6) equilibrium and Guo forcing, on shifted values
@@ -929,17 +979,17 @@ struct StepPhys {
 };
 // bytes of the arguments before it: row, nbb64, src, dst, n_tiles, lw,
 // nblocks, counter (and the boundary buffer)
-constexpr int STOCHASTIC = 16;  // flag beside lw in a step's shape argument
+constexpr int LW_MASK = 15, STOCHASTIC = 16;  // lw and a flag beside it in a step's shape argument
 constexpr int HOT_BYTES = 4 * 8 + 4 * 4;
 
-template <int ST, int MODEL, typename OffT, bool OPEN>
+template <int ST, int MODEL, typename OffT, bool OPEN, bool STAGED>
 __device__ __forceinline__ void step_tile(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst,
                                           int n_tiles, int shape, int nblocks, uint32_t counter, const uint64_t *bc) {
     using C = Codec<ST>;
     using S = typename C::S;
     using T = typename C::T;
     constexpr bool RN = C::RUNS;
-    const int tw = wave_tile<!RN>(shape & (STOCHASTIC - 1), nblocks);
+    const int tw = wave_tile<!RN>(shape & LW_MASK, nblocks);
     if (tw >= n_tiles) return;
     // consecutive launches walk the tiles in opposite directions, so a step
     // starts on the tiles the previous one wrote last (FP16 166.7 -> 164.6 us
@@ -996,38 +1046,42 @@ __device__ __forceinline__ void step_tile(const NbRow *row, const uint64_t *nbb6
             collide_model<T, MODEL>(d, T(P.rho_base()), T(P.omega()), T(P.kg()), Fx, Fy, Fz);
         }
     }
+    const auto store = [&](auto value) {
+        if constexpr (STAGED) store_tile_staged<S, RN, OffT>(dst, me, fl, lane, value);
+        else store_tile<S, RN, OffT, true, !RN>(dst, me, own, fl, lane, value);
+    };
     if constexpr (ST == LBM_F16S) {
         if (shape & STOCHASTIC) {
             // keyed on the node's position, not on where the tile is stored
             const uint32_t tile_seed = hash32(cx + hash32(cy + hash32(cz + hash32(counter))));
             const uint32_t seed = hash32(tile_seed + (uint32_t)lane);
             typename C::Pair pair = {};
-            store_tile<S, RN, OffT, true, !RN>(dst, me, own, fl, lane, [&](int i) {
-                return C::enc_sr_scaled(d[i], seed + (uint32_t)i * 0x9E3779B9u, pair);
-            });
+            store([&](int i) { return C::enc_sr_scaled(d[i], seed + (uint32_t)i * 0x9E3779B9u, pair); });
             return;
         }
-        store_tile<S, RN, OffT, true, !RN>(dst, me, own, fl, lane, [&](int i) { return C::enc_scaled(d[i]); });
+        store([&](int i) { return C::enc_scaled(d[i]); });
     } else {
-        store_tile<S, RN, OffT, true, !RN>(dst, me, own, fl, lane, [&](int i) { return C::enc(d[i], 1.0f); });
+        store([&](int i) { return C::enc(d[i], 1.0f); });
     }
 }
 
-// Open boundaries have a kernel of their own: in one kernel their parameters
+// Open boundaries have kernels of their own: in one kernel their parameters
 // and lane masks took scalar registers from every other step (12-16 spilled to
-// vector lanes, 6 without them).
-template <int ST, int MODEL, typename OffT>
-__global__ __launch_bounds__(512) void k_step(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst,
-                                              int n_tiles, int shape, int nblocks, uint32_t counter, Phys P) {
-    step_tile<ST, MODEL, OffT, false>(row, nbb64, src, dst, n_tiles, shape, nblocks, counter, nullptr);
-}
-
-template <int ST, int MODEL, typename OffT>
-__global__ __launch_bounds__(512) void k_step_open(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst,
-                                                   int n_tiles, int shape, int nblocks, uint32_t counter,
-                                                   const uint64_t *bc, Phys P) {
-    step_tile<ST, MODEL, OffT, true>(row, nbb64, src, dst, n_tiles, shape, nblocks, counter, bc);
-}
+// vector lanes, 6 without them).  So have steps that do not stage their
+// stores: a branch between the two ways at the end of one kernel cost 1-2%
+// either way.
+#define STEP_KERNEL(NAME, OPEN, STAGED, BC_PARAM, BC)                                                              \
+    template <int ST, int MODEL, typename OffT>                                                                    \
+    __global__ __launch_bounds__(512) void NAME(const NbRow *row, const uint64_t *nbb64, const char *src,          \
+                                                char *dst, int n_tiles, int shape, int nblocks, uint32_t counter,  \
+                                                BC_PARAM Phys P) {                                                 \
+        step_tile<ST, MODEL, OffT, OPEN, STAGED>(row, nbb64, src, dst, n_tiles, shape, nblocks, counter, BC);      \
+    }
+#define STEP_BC const uint64_t *bc,
+STEP_KERNEL(k_step, false, true, , nullptr)
+STEP_KERNEL(k_step_direct, false, false, , nullptr)
+STEP_KERNEL(k_step_open, true, true, STEP_BC, bc)
+STEP_KERNEL(k_step_open_direct, true, false, STEP_BC, bc)
 
 // the paper's measurement kernels (Section 4.1): kind 1 "read/write only",
 // kind 2 "propagation only"
@@ -1709,6 +1763,14 @@ struct AdjArgs {
     const NbRow *row, const uint64_t *nbb64, const char *s, const char *eta_in, int n_tiles, int lw, int nblocks, \
         uint32_t counter, AdjArgs a
 
+template <bool STAGED, typename T, typename OffT>
+__device__ __forceinline__ void store_adjoint(char *lattice, const Self<true, OffT> &me, uint64_t own, bool fl, int lane,
+                                              const T (&v)[Q]) {
+    const auto value = [&](int i) { return v[i]; };
+    if constexpr (STAGED) store_tile_staged<T, true, OffT>(lattice, me, fl, lane, value);
+    else store_tile<T, true, OffT, true>(lattice, me, own, fl, lane, value);
+}
+
 // seed: from s_{T-1}: g_T = S s_{T-1}, s_T = C(g_T), lam_T = dL/ds_T,
 // eta_T = J_T^T lam_T, grad = rho0 [(dC/dF)^T lam_T + dL/dF].  With
 // u_x = (sum c_x s - F_x/2)/rho (quasi-compressible) lam_T depends on s_T; with
@@ -1716,9 +1778,8 @@ struct AdjArgs {
 template <int ST, int MODEL, typename OffT>
 struct AdjWaves;
 
-template <int ST, int MODEL, typename OffT>
-__global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(1, AdjWaves<ST, MODEL, OffT>::max))) void k_adj_seed(ADJ_PARAMS) {
+template <int ST, int MODEL, typename OffT, bool STAGED>
+__device__ __forceinline__ void adj_seed_tile(ADJ_PARAMS) {
     constexpr int INC = MODEL & 1;
     using T = typename Codec<ST>::S;
     const int t = wave_tile(lw, nblocks);
@@ -1762,7 +1823,7 @@ __attribute__((amdgpu_waves_per_eu(1, AdjWaves<ST, MODEL, OffT>::max))) void k_a
         collide_jt_model<T, MODEL>(g, rb, lam, om, kg, Fx, Fy, Fz, eta, gx, gy, gz);
         gx += T(-0.5) * irT * inv_n;
     }
-    store_tile<T, true, OffT, true>(a.out, me, own, fl, lane, [&](int i) { return eta[i]; });
+    store_adjoint<STAGED, T, OffT>(a.out, me, own, fl, lane, eta);
     const FieldSlot fs(fbase, own);
     if (fl) {
         a.grad[fs.entry(0)] = a.P.rho0 * (double)gx;
@@ -1793,10 +1854,8 @@ struct AdjWaves {
     static constexpr int max = (ST == 0 && MODEL >= 2) ? 2 : 8;
 };
 
-template <int ST, int MODEL, typename OffT>
-__global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(AdjWaves<ST, MODEL, OffT>::value, AdjWaves<ST, MODEL, OffT>::max))) void k_adj_step(
-    ADJ_PARAMS) {
+template <int ST, int MODEL, typename OffT, bool STAGED>
+__device__ __forceinline__ void adj_step_tile(ADJ_PARAMS) {
     using T = typename Codec<ST>::S;
     const int tw = wave_tile(lw, nblocks);
     if (tw >= n_tiles) return;
@@ -1842,12 +1901,12 @@ __attribute__((amdgpu_waves_per_eu(AdjWaves<ST, MODEL, OffT>::value, AdjWaves<ST
             a.grad[fs.entry(2)] += a.P.rho0 * (double)gz;
         }
     }
-    store_tile<T, true, OffT, true>(a.out, me, own, fl, lane, [&](int i) { return eta[i]; });
+    store_adjoint<STAGED, T, OffT>(a.out, me, own, fl, lane, eta);
 }
 
 // final: lam_0 = S^T eta_1
-template <int ST, int MODEL, typename OffT>
-__global__ __launch_bounds__(512) void k_adj_final(ADJ_PARAMS) {
+template <int ST, int MODEL, typename OffT, bool STAGED>
+__device__ __forceinline__ void adj_final_tile(ADJ_PARAMS) {
     using T = typename Codec<ST>::S;
     const int t = wave_tile(lw, nblocks);
     if (t >= n_tiles) return;
@@ -1862,8 +1921,23 @@ __global__ __launch_bounds__(512) void k_adj_final(ADJ_PARAMS) {
     if (fl) {
         gather_all<true, true, T, OffT>(lam, h, eta_in, me, lane);
     }
-    store_tile<T, true, OffT, true>(a.out, me, own, fl, lane, [&](int i) { return lam[i]; });
+    store_adjoint<STAGED, T, OffT>(a.out, me, own, fl, lane, lam);
 }
+
+#define ADJ_NAMES row, nbb64, s, eta_in, n_tiles, lw, nblocks, counter, a
+#define ADJ_KERNEL(NAME, BODY, STAGED, ATTRIBUTES)                                 \
+    template <int ST, int MODEL, typename OffT>                                    \
+    __global__ __launch_bounds__(512) ATTRIBUTES void NAME(ADJ_PARAMS) {           \
+        BODY<ST, MODEL, OffT, STAGED>(ADJ_NAMES);                                  \
+    }
+#define SEED_WAVES __attribute__((amdgpu_waves_per_eu(1, AdjWaves<ST, MODEL, OffT>::max)))
+#define STEP_WAVES __attribute__((amdgpu_waves_per_eu(AdjWaves<ST, MODEL, OffT>::value, AdjWaves<ST, MODEL, OffT>::max)))
+ADJ_KERNEL(k_adj_seed, adj_seed_tile, true, SEED_WAVES)
+ADJ_KERNEL(k_adj_seed_direct, adj_seed_tile, false, SEED_WAVES)
+ADJ_KERNEL(k_adj_step, adj_step_tile, true, STEP_WAVES)
+ADJ_KERNEL(k_adj_step_direct, adj_step_tile, false, STEP_WAVES)
+ADJ_KERNEL(k_adj_final, adj_final_tile, true, )
+ADJ_KERNEL(k_adj_final_direct, adj_final_tile, false, )
 
 // ---------------------------------------------------------------------------
 // bandwidth probes: what the part sustains for plain streaming, the practical
@@ -1943,17 +2017,33 @@ static KArgs make_args(const Launch &L, const Phys &P, const void *src, void *ds
 // are in scalar registers when a wave starts instead of a memory read away.
 #define KHOT(a) (a).tb.row, (a).tb.nbb64, (a).src, (a).dst, (a).n_tiles, (a).lw, (a).nblocks
 
+// Whether a launch stages its stores: with more tiles than are in flight at
+// once (4096 of FP64, 7168 of FP32), where the waves that wait for the LDS are
+// covered by others (FP64, us a step, direct -> staged: 512 tiles 5.7 -> 6.2,
+// 3300 13.3 -> 13.5, 6320 21.5 -> 21.5, 8830 25.3 -> 24.6, 23605 62.4 -> 60.4,
+// 169669 388 -> 372); within the 64 KB that a workgroup is sure to get; to
+// lattices on a 16-byte boundary.
+constexpr int STAGE_MIN_TILES = 6144;
+template <typename S>
+static bool stage_stores(const Launch &L, const void *dst) {
+    return L.n_tiles >= STAGE_MIN_TILES && L.tpw * STAGE_BYTES<S> <= 65536 && reinterpret_cast<uintptr_t>(dst) % 16 == 0;
+}
+
 static dim3 block_of(const Launch &L) { return dim3(64 * L.tpw); }
 
 template <int ST, int MODEL, typename OffT>
 static hipError_t step_o(const Launch &L, KArgs a) {
+    using S = typename Codec<ST>::S;
     if (a.P.f16_stochastic) a.lw |= STOCHASTIC;
-    if (a.P.bc)
-        hipLaunchKernelGGL((k_step_open<ST, MODEL, OffT>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a),
-                           a.P.launch_counter, a.P.bc, a.P);
-    else
-        hipLaunchKernelGGL((k_step<ST, MODEL, OffT>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a),
-                           a.P.launch_counter, a.P);
+    const bool staged = stage_stores<S>(L, a.dst);
+    const size_t lds = staged ? (size_t)L.tpw * STAGE_BYTES<S> : 0;
+    if (a.P.bc) {
+        const auto fn = staged ? k_step_open<ST, MODEL, OffT> : k_step_open_direct<ST, MODEL, OffT>;
+        hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), lds, L.stream, KHOT(a), a.P.launch_counter, a.P.bc, a.P);
+    } else {
+        const auto fn = staged ? k_step<ST, MODEL, OffT> : k_step_direct<ST, MODEL, OffT>;
+        hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), lds, L.stream, KHOT(a), a.P.launch_counter, a.P);
+    }
     return hipGetLastError();
 }
 
@@ -2205,23 +2295,34 @@ hipError_t launch_tiles_to_dense(const Launch &L, const void *tile_buf, int ncom
 // model; the final reverse gather has no model
 template <int ST, int MODEL, typename OffT>
 struct SeedK {
-    static constexpr auto fn = k_adj_seed<ST, MODEL, OffT>;
+    static constexpr auto staged = k_adj_seed<ST, MODEL, OffT>, direct = k_adj_seed_direct<ST, MODEL, OffT>;
 };
 template <int ST, int MODEL, typename OffT>
 struct StepK {
-    static constexpr auto fn = k_adj_step<ST, MODEL, OffT>;
+    static constexpr auto staged = k_adj_step<ST, MODEL, OffT>, direct = k_adj_step_direct<ST, MODEL, OffT>;
 };
 template <int ST, int MODEL, typename OffT>
 struct FinalK {
-    static constexpr auto fn = k_adj_final<ST, LBM_QUASI_COMPRESSIBLE, OffT>;
+    static constexpr auto staged = k_adj_final<ST, LBM_QUASI_COMPRESSIBLE, OffT>,
+                          direct = k_adj_final_direct<ST, LBM_QUASI_COMPRESSIBLE, OffT>;
 };
-
 using AdjFn = void (*)(ADJ_PARAMS);
 
-template <template <int, int, typename> class K, int MODEL>
-static AdjFn adj_fn(const Launch &L, bool f32) {
-    if (L.off32) return f32 ? K<LBM_F32, MODEL, uint32_t>::fn : K<LBM_F64, MODEL, uint32_t>::fn;
-    return f32 ? K<LBM_F32, MODEL, uint64_t>::fn : K<LBM_F64, MODEL, uint64_t>::fn;
+template <template <int, int, typename> class K, int ST, int MODEL>
+static AdjFn adj_fn(const Launch &L, bool staged) {
+    if (L.off32) return staged ? K<ST, MODEL, uint32_t>::staged : K<ST, MODEL, uint32_t>::direct;
+    return staged ? K<ST, MODEL, uint64_t>::staged : K<ST, MODEL, uint64_t>::direct;
+}
+
+template <template <int, int, typename> class K, int ST>
+static AdjFn adj_fn(const Launch &L, bool staged, int model) {
+    switch (model) {
+    case LBM_QUASI_COMPRESSIBLE: return adj_fn<K, ST, LBM_QUASI_COMPRESSIBLE>(L, staged);
+    case LBM_INCOMPRESSIBLE: return adj_fn<K, ST, LBM_INCOMPRESSIBLE>(L, staged);
+    case LBM_MRT_QUASI_COMPRESSIBLE: return adj_fn<K, ST, LBM_MRT_QUASI_COMPRESSIBLE>(L, staged);
+    case LBM_MRT_INCOMPRESSIBLE: return adj_fn<K, ST, LBM_MRT_INCOMPRESSIBLE>(L, staged);
+    }
+    return nullptr;
 }
 
 template <template <int, int, typename> class K>
@@ -2229,19 +2330,15 @@ static hipError_t launch_adj(const Launch &L, const Phys &P, const void *s, cons
                              double *grad) {
     if (L.n_tiles == 0) return hipSuccess;
     const bool f32 = P.storage == LBM_F32;
-    AdjFn fn = nullptr;
-    switch (P.model) {
-    case LBM_QUASI_COMPRESSIBLE: fn = adj_fn<K, LBM_QUASI_COMPRESSIBLE>(L, f32); break;
-    case LBM_INCOMPRESSIBLE: fn = adj_fn<K, LBM_INCOMPRESSIBLE>(L, f32); break;
-    case LBM_MRT_QUASI_COMPRESSIBLE: fn = adj_fn<K, LBM_MRT_QUASI_COMPRESSIBLE>(L, f32); break;
-    case LBM_MRT_INCOMPRESSIBLE: fn = adj_fn<K, LBM_MRT_INCOMPRESSIBLE>(L, f32); break;
-    default: return hipErrorInvalidValue;
-    }
+    const bool staged = f32 ? stage_stores<float>(L, out) : stage_stores<double>(L, out);
+    const AdjFn fn = f32 ? adj_fn<K, LBM_F32>(L, staged, P.model) : adj_fn<K, LBM_F64>(L, staged, P.model);
+    if (!fn) return hipErrorInvalidValue;
     AdjArgs a;
     a.out = reinterpret_cast<char *>(out);
     a.grad = grad;
     a.P = P;
-    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), 0, L.stream, L.tb.row, L.tb.nbb64,
+    const size_t lds = staged ? (size_t)L.tpw * (f32 ? STAGE_BYTES<float> : STAGE_BYTES<double>) : 0;
+    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), lds, L.stream, L.tb.row, L.tb.nbb64,
                        reinterpret_cast<const char *>(s), reinterpret_cast<const char *>(eta_in), L.n_tiles,
                        __builtin_ctz((unsigned)L.tpw), L.grid, P.launch_counter, a);
     return hipGetLastError();
