@@ -1085,7 +1085,7 @@ STEP_KERNEL(k_step_open_direct, true, false, STEP_BC, bc)
 
 // the paper's measurement kernels (Section 4.1): kind 1 "read/write only",
 // kind 2 "propagation only"
-template <typename S, bool RN, int KIND, typename OffT>
+template <typename S, bool RN, int KIND, typename OffT, bool STAGED>
 __global__ __launch_bounds__(512) void k_calib(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst, int n_tiles,
                                                int lw, int nblocks, const TileRec *rec) {
     const int t = wave_tile<!RN>(lw, nblocks);
@@ -1115,7 +1115,9 @@ __global__ __launch_bounds__(512) void k_calib(const NbRow *row, const uint64_t 
             gather_all<false, RN, S, OffT>(v, h, src, me, lane);
         }
     }
-    store_tile<S, RN, OffT, true>(dst, me, own, fl, lane, [&](int i) { return v[i]; });
+    const auto value = [&](int i) { return v[i]; };  // as a step stores
+    if constexpr (STAGED) store_tile_staged<S, RN, OffT>(dst, me, fl, lane, value);
+    else store_tile<S, RN, OffT, true>(dst, me, own, fl, lane, value);
 }
 
 // The paper's intra-tile layout study (Section 3.3, Eqs. 11-13; Table 5):
@@ -2074,16 +2076,20 @@ hipError_t launch_step(const Launch &L, const Phys &P, const void *src, void *ds
     return hipErrorInvalidValue;
 }
 
+template <int ST, int KIND, typename OffT>
+static hipError_t calib_o(const Launch &L, const KArgs &a) {
+    using C = Codec<ST>;
+    using S = typename C::S;
+    const bool staged = stage_stores<S>(L, a.dst);
+    const auto fn = staged ? k_calib<S, C::RUNS, KIND, OffT, true> : k_calib<S, C::RUNS, KIND, OffT, false>;
+    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), staged ? (size_t)L.tpw * STAGE_BYTES<S> : 0, L.stream, KHOT(a),
+                       a.tb.rec);
+    return hipGetLastError();
+}
+
 template <int ST, int KIND>
 static hipError_t calib_t(const Launch &L, const KArgs &a) {
-    using C = Codec<ST>;
-    if (L.off32)
-        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint32_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a),
-                           a.tb.rec);
-    else
-        hipLaunchKernelGGL((k_calib<typename C::S, C::RUNS, KIND, uint64_t>), dim3(L.grid), block_of(L), 0, L.stream, KHOT(a),
-                           a.tb.rec);
-    return hipGetLastError();
+    return L.off32 ? calib_o<ST, KIND, uint32_t>(L, a) : calib_o<ST, KIND, uint64_t>(L, a);
 }
 
 template <typename S, int LS>
