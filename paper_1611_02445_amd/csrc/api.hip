@@ -351,6 +351,11 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     if (n > 0 && c->device >= 0 && hipHostMalloc(&pinned, NSUM * sizeof(double), hipHostMallocDefault) == hipSuccess)
         c->host_sums = reinterpret_cast<double *>(pinned);
 
+    // every byte offset into a lattice (an adjoint lattice has the layout and
+    // size of the state) must fit 32 bits for the 32-bit kernels; the others
+    // get 128-byte lines, where every tile's data begins
+    const bool off32 = c->state_bytes <= (size_t)UINT32_MAX && !c->params.wide_offsets;
+    const uint64_t line = 128 / storage_size(params->storage);
     const TableLayout lay(n, grid_tiles(tiles->nx, tiles->ny, tiles->nz));
     if (n > 0) try {
         // device tile d holds discovery tile perm[d]; neighbour numbers are
@@ -359,11 +364,10 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
         processing_order(tiles, c->params.tile_order, perm);
         inv.assign((size_t)n, 0);
         for (int64_t d = 0; d < n; ++d) inv[perm[d]] = (int32_t)d;
-        std::vector<unsigned char> host(lay.total, 0);
+        std::vector<unsigned char> host(lay.used, 0);
         c->corner.assign((size_t)n * 3, 0);
         TileRec *rec = reinterpret_cast<TileRec *>(host.data() + lay.rec_off);
         NbRow *row = reinterpret_cast<NbRow *>(host.data() + lay.row_off);
-        uint64_t *nbb64 = reinterpret_cast<uint64_t *>(host.data() + lay.nbb64_off);
         int32_t *xyz = reinterpret_cast<int32_t *>(host.data() + lay.xyz_off);
         uint64_t *fbase = reinterpret_cast<uint64_t *>(host.data() + lay.fld_off);
         int32_t *map = reinterpret_cast<int32_t *>(host.data() + lay.map_off);
@@ -395,13 +399,12 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
                 const int32_t v = tiles->nbr[27 * i + k];
                 const TileRec r = v < 0 ? TileRec{0, 0} : rec[inv[v]];
                 row[d].mask[s] = r.mask;
-                row[d].base32[s] = (uint32_t)r.base;
-                nbb64[NB_STRIDE * d + s] = r.base;
+                row[d].base32[s] = (uint32_t)(off32 ? r.base : r.base / line);
             }
             row[d].fbase = fbase[d];
             for (int a = 0; a < 3; ++a) row[d].xyz[a] = xyz[4 * d + a];
         }
-        hipError_t e = hipMemcpyAsync(tables, host.data(), lay.total, hipMemcpyHostToDevice, c->stream);
+        hipError_t e = hipMemcpyAsync(tables, host.data(), lay.used, hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) {
             delete c;
@@ -418,17 +421,16 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     c->L.grid = (int)((n + c->L.tpw - 1) / c->L.tpw);
     c->L.tb.rec = reinterpret_cast<const TileRec *>(tb + lay.rec_off);
     c->L.tb.row = reinterpret_cast<const NbRow *>(tb + lay.row_off);
-    c->L.tb.nbb64 = reinterpret_cast<const uint64_t *>(tb + lay.nbb64_off);
     c->L.tb.xyz = reinterpret_cast<const int32_t *>(tb + lay.xyz_off);
     c->L.tb.fbase = reinterpret_cast<const uint64_t *>(tb + lay.fld_off);
     c->L.tb.map = reinterpret_cast<const int32_t *>(tb + lay.map_off);
-    // every byte offset into a lattice (an adjoint lattice has the layout and
-    // size of the state) must fit 32 bits for the 32-bit kernels
-    c->L.off32 = c->state_bytes <= (size_t)UINT32_MAX && !c->params.wide_offsets;
-    // The FP64 LBMRT adjoint steps hold 2 waves per SIMD (194-250 VGPRs); with
-    // one tile per workgroup instead of four they run 4-5% faster on a 128^3
-    // sphere pack, while the LBGK adjoint kernels are fastest at four.  Applies
-    // only when the caller left the workgroup size to the library.
+    c->L.off32 = off32;
+    // The FP64 LBMRT adjoint steps hold 2-3 waves per SIMD (146-240 VGPRs); with
+    // one tile per workgroup instead of four they run 4-5% faster with direct
+    // stores and with staged ones 1-2% on a 128^3 sphere pack (84.3 against
+    // 86.0 us) and as fast on a 192^3 one (279.8 against 281.7), while the LBGK
+    // adjoint kernels are fastest at four.  Applies only when the caller left
+    // the workgroup size to the library.
     c->LA = c->L;
     if (params->tiles_per_wg == 0 && params->storage == LBM_F64 && params->model >= LBM_MRT_QUASI_COMPRESSIBLE) {
         c->LA.tpw = 1;

@@ -145,11 +145,12 @@ inline uint64_t run_elems(uint64_t mask, int storage) {
 // device table layout inside the caller's `tables` buffer
 //   [rec_off]    TileRec per tile: fluid mask, element offset of its data
 //   [row_off]    NbRow per tile, 256 bytes on a 256-byte boundary: the fluid
-//                masks and 32-bit element offsets of the 19 tiles a D3Q19 step
+//                masks and 32-bit data offsets of the 19 tiles a D3Q19 step
 //                reads from (the tile itself, 6 face and 12 edge neighbours;
 //                corners are never needed; mask 0 for a missing tile), the
-//                entry offset of the tile's per-node field run and its corner
-//   [nbb64_off]  uint64 [n_tiles][20]: the 19 element offsets in 64 bits
+//                offsets in elements for the kernels with 32-bit
+//                lattice offsets and in lines of 128 bytes, where every
+//                tile's data begins, for the others; the entry offset of the tile's per-node field run and its corner
 //   [xyz_off]    int32  [n_tiles][4]: corner x, y, z, 0
 //   [fld_off]    uint64 [n_tiles]: entry offset of the tile's per-node field run
 //   [map_off]    int32  [tz][ty][tx]: device tile number of each tile of the
@@ -164,7 +165,6 @@ struct TileRec {
     uint64_t mask;
     uint64_t base;
 };
-constexpr int NB_STRIDE = 20;
 // slot of neighbour k = (dx+1) + 3(dy+1) + 9(dz+1) in a neighbourhood row,
 // -1 for the 8 corners
 constexpr int nb_slot(int k) {
@@ -191,24 +191,24 @@ struct alignas(64) NbRow {
 static_assert(sizeof(NbRow) == 256, "a row is two whole 128-byte lines");
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct TableLayout {
-    size_t rec_off, row_off, nbb64_off, xyz_off, fld_off, map_off, total;
+    size_t rec_off, row_off, xyz_off, fld_off, map_off, used, total;
     // n_grid: tiles of the whole box, kept or not
     TableLayout(int64_t n_tiles, int64_t n_grid) {
         const size_t n = (size_t)n_tiles;
         rec_off = 0;
         row_off = align_up(rec_off + n * sizeof(TileRec), 256);
-        nbb64_off = align_up(row_off + n * sizeof(NbRow), 256);
-        xyz_off = align_up(nbb64_off + n * NB_STRIDE * 8, 256);
+        xyz_off = align_up(row_off + n * sizeof(NbRow), 256);
         fld_off = align_up(xyz_off + n * 16, 256);
         map_off = align_up(fld_off + n * 8, 256);
-        total = n ? align_up(map_off + (size_t)n_grid * 4, 256) : 0;
+        used = n ? align_up(map_off + (size_t)n_grid * 4, 256) : 0;
+        // callers are promised that no build asks for less than 432 bytes a tile
+        total = used < n * 432 ? align_up(n * 432, 256) : used;
     }
 };
 
 struct DevTables {
     const TileRec *rec;
     const NbRow *row;
-    const uint64_t *nbb64;
     const int32_t *xyz;
     const uint64_t *fbase;
     const int32_t *map;

@@ -193,14 +193,22 @@ struct RowRegs {
     __device__ __forceinline__ uint32_t xyz(int c) const { return dword((int)offsetof(NbRow, xyz) / 4 + c); }
 };
 
-template <typename OffT>
-__device__ __forceinline__ void load_nbhd(Nbhd<OffT> &h, const RowRegs &r, const uint64_t *nbb64, int t) {
+// A tile's data starts on a line of 128 bytes, so with 64-bit offsets the row
+// holds its line number (all of 512 GB) and the element offset is a shift
+// away.  A table of 64-bit offsets beside the rows was a second read, waited
+// for between the gathers (256^3 pack with 64-bit offsets, us a step: FP64
+// 377 -> 361, FP32 222 -> 208, FP16 194 -> 165; FP64 LBMRT 410 -> 391, FP32
+// 253 -> 228; FP32 384^3 box 1646 -> 1588; FP64 384^3 box 3198 -> 3257, where
+// waves that start their gathers later get in each other's way less).
+template <typename S, typename OffT>
+__device__ __forceinline__ void load_nbhd(Nbhd<OffT> &h, const RowRegs &r) {
+    constexpr int LINE = __builtin_ctz(128 / sizeof(S));
 #pragma unroll
     for (int k = 0; k < 27; ++k) {
         const int s = nb_slot(k);
         h.m[k] = s < 0 ? 0ull : r.mask(s);
         if constexpr (std::is_same<OffT, uint32_t>::value) h.base[k] = s < 0 ? 0u : r.base32(s);
-        else h.base[k] = s < 0 ? 0ull : nbb64[(size_t)t * NB_STRIDE + s];
+        else h.base[k] = s < 0 ? 0ull : (uint64_t)r.base32(s) << LINE;
     }
 }
 constexpr int OWN = 13;  // the tile itself in its neighbourhood
@@ -977,14 +985,14 @@ struct StepPhys {
     __device__ __forceinline__ float inv_scale() const { return f32(3); }
     __device__ __forceinline__ const Phys &all() const { return *(const Phys *)at; }
 };
-// bytes of the arguments before it: row, nbb64, src, dst, n_tiles, lw,
-// nblocks, counter (and the boundary buffer)
+// bytes of the arguments before it: row, src, dst, n_tiles, lw, nblocks,
+// counter (and the boundary buffer)
 constexpr int LW_MASK = 15, STOCHASTIC = 16;  // lw and a flag beside it in a step's shape argument
-constexpr int HOT_BYTES = 4 * 8 + 4 * 4;
+constexpr int HOT_BYTES = 3 * 8 + 4 * 4;
 
 template <int ST, int MODEL, typename OffT, bool OPEN, bool STAGED>
-__device__ __forceinline__ void step_tile(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst,
-                                          int n_tiles, int shape, int nblocks, uint32_t counter, const uint64_t *bc) {
+__device__ __forceinline__ void step_tile(const NbRow *row, const char *src, char *dst, int n_tiles,
+                                          int shape, int nblocks, uint32_t counter, const uint64_t *bc) {
     using C = Codec<ST>;
     using S = typename C::S;
     using T = typename C::T;
@@ -1001,7 +1009,7 @@ __device__ __forceinline__ void step_tile(const NbRow *row, const uint64_t *nbb6
     if constexpr (OPEN) any = bc[9 * (size_t)t];
     const RowRegs r(row, t);
     Nbhd<OffT> h;
-    load_nbhd(h, r, nbb64, t);
+    load_nbhd<S>(h, r);
     const uint64_t fbase = r.fbase();
     // the tile's position keys the stochastic rounding
     uint32_t cx = 0, cy = 0, cz = 0;
@@ -1072,10 +1080,10 @@ __device__ __forceinline__ void step_tile(const NbRow *row, const uint64_t *nbb6
 // either way.
 #define STEP_KERNEL(NAME, OPEN, STAGED, BC_PARAM, BC)                                                              \
     template <int ST, int MODEL, typename OffT>                                                                    \
-    __global__ __launch_bounds__(512) void NAME(const NbRow *row, const uint64_t *nbb64, const char *src,          \
+    __global__ __launch_bounds__(512) void NAME(const NbRow *row, const char *src,                                 \
                                                 char *dst, int n_tiles, int shape, int nblocks, uint32_t counter,  \
                                                 BC_PARAM Phys P) {                                                 \
-        step_tile<ST, MODEL, OffT, OPEN, STAGED>(row, nbb64, src, dst, n_tiles, shape, nblocks, counter, BC);      \
+        step_tile<ST, MODEL, OffT, OPEN, STAGED>(row, src, dst, n_tiles, shape, nblocks, counter, BC);             \
     }
 #define STEP_BC const uint64_t *bc,
 STEP_KERNEL(k_step, false, true, , nullptr)
@@ -1086,7 +1094,7 @@ STEP_KERNEL(k_step_open_direct, true, false, STEP_BC, bc)
 // the paper's measurement kernels (Section 4.1): kind 1 "read/write only",
 // kind 2 "propagation only"
 template <typename S, bool RN, int KIND, typename OffT, bool STAGED>
-__global__ __launch_bounds__(512) void k_calib(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst, int n_tiles,
+__global__ __launch_bounds__(512) void k_calib(const NbRow *row, const char *src, char *dst, int n_tiles,
                                                int lw, int nblocks, const TileRec *rec) {
     const int t = wave_tile<!RN>(lw, nblocks);
     if (t >= n_tiles) return;
@@ -1096,7 +1104,7 @@ __global__ __launch_bounds__(512) void k_calib(const NbRow *row, const uint64_t 
         h.m[OWN] = rec[t].mask;
         h.base[OWN] = (OffT)rec[t].base;
     } else {
-        load_nbhd(h, RowRegs(row, t), nbb64, t);
+        load_nbhd<S>(h, RowRegs(row, t));
     }
     const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
@@ -1171,14 +1179,14 @@ __device__ __forceinline__ void gather_layout_all(S (&v)[Q], const Nbhd<OffT> &h
 }
 
 template <typename S, int LS, typename OffT>
-__global__ __launch_bounds__(512) void k_calib_layout(const NbRow *row, const uint64_t *nbb64, const char *src, char *dst, int n_tiles,
+__global__ __launch_bounds__(512) void k_calib_layout(const NbRow *row, const char *src, char *dst, int n_tiles,
                                                int lw, int nblocks) {
     const int t = wave_tile(lw, nblocks);
     if (t >= n_tiles) return;
     const int lane = (int)(threadIdx.x & 63);
     const int x = lane & 3, y = (lane >> 2) & 3, z = lane >> 4;
     Nbhd<OffT> h;
-    load_nbhd(h, RowRegs(row, t), nbb64, t);
+    load_nbhd<S>(h, RowRegs(row, t));
     const Self<false, OffT> me(h, lane);
     S v[Q];
     gather_layout_all<LS, S, OffT>(v, h, src, me, x, y, z, lane, std::make_integer_sequence<int, Q>{});
@@ -1752,7 +1760,7 @@ __device__ __forceinline__ void collide_jt_model(const T (&d)[Q], T rho_base, co
         collide_jt<T, (MODEL & 1)>(d, rho_base, lam, omega, kg, Fx, Fy, Fz, eta, gx, gy, gz);
 }
 
-// The first arguments, twelve registers, are what a wave needs before it can
+// The first arguments, ten registers, are what a wave needs before it can
 // issue its gathers: the build has them preloaded.
 struct AdjArgs {
     char *out;          // adjoint lattice written
@@ -1762,7 +1770,7 @@ struct AdjArgs {
 //   s       forward lattice feeding the forward gather
 //   eta_in  adjoint lattice feeding the reverse gather
 #define ADJ_PARAMS                                                                                                 \
-    const NbRow *row, const uint64_t *nbb64, const char *s, const char *eta_in, int n_tiles, int lw, int nblocks, \
+    const NbRow *row, const char *s, const char *eta_in, int n_tiles, int lw, int nblocks,                        \
         uint32_t counter, AdjArgs a
 
 template <bool STAGED, typename T, typename OffT>
@@ -1789,7 +1797,7 @@ __device__ __forceinline__ void adj_seed_tile(ADJ_PARAMS) {
     const int lane = (int)(threadIdx.x & 63);
     const RowRegs r(row, t);
     Nbhd<OffT> h;
-    load_nbhd(h, r, nbb64, t);
+    load_nbhd<T>(h, r);
     const uint64_t fbase = r.fbase();
     const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
@@ -1868,7 +1876,7 @@ __device__ __forceinline__ void adj_step_tile(ADJ_PARAMS) {
     const int lane = (int)(threadIdx.x & 63);
     const RowRegs r(row, t);
     Nbhd<OffT> h;
-    load_nbhd(h, r, nbb64, t);
+    load_nbhd<T>(h, r);
     const uint64_t fbase = r.fbase();
     const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
@@ -1915,7 +1923,7 @@ __device__ __forceinline__ void adj_final_tile(ADJ_PARAMS) {
     const int lane = (int)(threadIdx.x & 63);
     const RowRegs r(row, t);
     Nbhd<OffT> h;
-    load_nbhd(h, r, nbb64, t);
+    load_nbhd<T>(h, r);
     const uint64_t own = h.m[OWN];
     const bool fl = lane_on(own);
     const Self<true, OffT> me(h, lane);
@@ -1926,7 +1934,7 @@ __device__ __forceinline__ void adj_final_tile(ADJ_PARAMS) {
     store_adjoint<STAGED, T, OffT>(a.out, me, own, fl, lane, lam);
 }
 
-#define ADJ_NAMES row, nbb64, s, eta_in, n_tiles, lw, nblocks, counter, a
+#define ADJ_NAMES row, s, eta_in, n_tiles, lw, nblocks, counter, a
 #define ADJ_KERNEL(NAME, BODY, STAGED, ATTRIBUTES)                                 \
     template <int ST, int MODEL, typename OffT>                                    \
     __global__ __launch_bounds__(512) ATTRIBUTES void NAME(ADJ_PARAMS) {           \
@@ -2017,7 +2025,7 @@ static KArgs make_args(const Launch &L, const Phys &P, const void *src, void *ds
 // of every kernel that gathers: the build has the command processor preload
 // the first twelve argument registers (-amdgpu-kernarg-preload-count), so they
 // are in scalar registers when a wave starts instead of a memory read away.
-#define KHOT(a) (a).tb.row, (a).tb.nbb64, (a).src, (a).dst, (a).n_tiles, (a).lw, (a).nblocks
+#define KHOT(a) (a).tb.row, (a).src, (a).dst, (a).n_tiles, (a).lw, (a).nblocks
 
 // Whether a launch stages its stores: with more tiles than are in flight at
 // once (4096 of FP64, 7168 of FP32), where the waves that wait for the LDS are
@@ -2344,7 +2352,7 @@ static hipError_t launch_adj(const Launch &L, const Phys &P, const void *s, cons
     a.grad = grad;
     a.P = P;
     const size_t lds = staged ? (size_t)L.tpw * (f32 ? STAGE_BYTES<float> : STAGE_BYTES<double>) : 0;
-    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), lds, L.stream, L.tb.row, L.tb.nbb64,
+    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), lds, L.stream, L.tb.row,
                        reinterpret_cast<const char *>(s), reinterpret_cast<const char *>(eta_in), L.n_tiles,
                        __builtin_ctz((unsigned)L.tpw), L.grid, P.launch_counter, a);
     return hipGetLastError();
