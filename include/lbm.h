@@ -264,8 +264,8 @@ int lbm_current_state(lbm_ctx *ctx, void **state);
  *            fluid node count, max |u|, number of fluid nodes with a
  *            non-finite rho or u, and sum u_x (the adjoint's loss is
  *            sums[7] / sums[4], the mean x-velocity over fluid nodes).
- *            Reduced in FP64 in a fixed order (bitwise reproducible for the
- *            same tiles and the same choice of fields).
+ *            Reduced in FP64 in a fixed order (bitwise reproducible, and the
+ *            same bits whichever fields are asked for).
  * Synchronises the stream.  Returns LBM_E_NUMERIC (after filling sums and the
  * fields) when a non-finite value was found, or, with check_u_max set, when
  * sums[5] = max |u| exceeds LBM_U_MAX. */

@@ -1255,8 +1255,8 @@ __device__ __forceinline__ double wave_max(double v) {
 // ---------------------------------------------------------------------------
 // a dense box, walked by rows of 16 nodes along x
 // ---------------------------------------------------------------------------
-// One workgroup of 4 waves takes 4 tiles side by side along x, wave w their
-// z-plane w: lane l is node (l & 15, l >> 4) of the 16 x 4 nodes of that plane,
+// One workgroup of 4 waves takes a group of 4 tiles side by side along x, wave w
+// their z-plane w: lane l is node (l & 15, l >> 4) of the 16 x 4 nodes of that plane,
 // in tile l >> 2 & 3.  A store of a dense FP64 array is then 4 whole 128-byte
 // lines (a wave on its own tile writes 16 pieces of 32 bytes), the nodes of
 // tiles that were dropped are written too, so no pass over the array clears it
@@ -1346,23 +1346,37 @@ struct DenseWalk {
 // them once at the end: a butterfly per tile (96 cross-lane moves, through the
 // LDS pipe) took longer than reading the tile.  Every workgroup leaves one row
 // of partial sums; the work and the order of every addition follow from the
-// launch shape alone, so the sums are bitwise reproducible.
+// tiles and the box alone, so the sums are bitwise reproducible.
+// A lane adds up one node after another, where a butterfly per tile adds them
+// in pairs: what each addition rounds off is kept beside the sum and added at
+// the end, so the longer chain costs no accuracy.
+
+// s + c += x, with c what the additions to s have rounded off so far (the
+// two-term sum of D. E. Knuth, TAOCP vol. 2, 4.2.2)
+__device__ __forceinline__ void add_kept(double &s, double &c, double x) {
+    const double t = s + x, b = t - s;
+    c += (s - (t - b)) + (x - b);
+    s = t;
+}
+// a sum that has overflowed or met a NaN is what plain additions make of it
+__device__ __forceinline__ double kept_total(double s, double c) { return isfinite(s) ? s + c : s; }
+
 struct MacroSums {
-    double v[NSUM];
+    double v[NSUM], kept[NSUM];  // kept: of the five sums that round
     __device__ __forceinline__ MacroSums() {
 #pragma unroll
-        for (int c = 0; c < NSUM; ++c) v[c] = 0.0;
+        for (int c = 0; c < NSUM; ++c) v[c] = kept[c] = 0.0;
     }
     __device__ __forceinline__ void add(double rho, double ux, double uy, double uz) {
         const bool finite = isfinite(rho) && isfinite(ux) && isfinite(uy) && isfinite(uz);
-        v[0] += rho;
-        v[1] += rho * ux;
-        v[2] += rho * uy;
-        v[3] += rho * uz;
+        add_kept(v[0], kept[0], rho);
+        add_kept(v[1], kept[1], rho * ux);
+        add_kept(v[2], kept[2], rho * uy);
+        add_kept(v[3], kept[3], rho * uz);
         v[4] += 1.0;
         if (finite) v[5] = fmax(v[5], sqrt(ux * ux + uy * uy + uz * uz));
         else v[6] += 1.0;
-        v[7] += ux;
+        add_kept(v[7], kept[7], ux);
     }
     // by all threads of a workgroup of MACRO_THREADS, into its row of partials
     __device__ __forceinline__ void store(double *partials);
@@ -1373,7 +1387,7 @@ __device__ __forceinline__ void MacroSums::store(double *partials) {
     const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
 #pragma unroll
     for (int c = 0; c < NSUM; ++c) {
-        const double r = c == 5 ? wave_max(v[c]) : wave_sum(v[c]);
+        const double r = c == 5 ? wave_max(v[c]) : wave_sum(kept_total(v[c], kept[c]));
         if (lane == 0) sh[wave][c] = r;
     }
     __syncthreads();
@@ -1409,15 +1423,32 @@ __device__ __forceinline__ void macro_node(const Phys &P, double Fx, double Fy, 
     }
 }
 
-// the sums alone, tile after tile: no dropped tile is visited
+// rho and the velocity of this lane's node of a tile that holds it
 template <int ST>
-__global__ __launch_bounds__(MACRO_THREADS) void k_sums(KArgs a, double *partials) {
+__device__ __forceinline__ void macro_of_tile(const KArgs &a, int t, const TileRec &rec, int lane, double &rho,
+                                              double &ux, double &uy, double &uz) {
     using C = Codec<ST>;
     using S = typename C::S;
     using T = typename C::T;
+    const Self<C::RUNS, uint64_t> me(rec, lane);
+    S raw[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) raw[i] = load_elem<uint64_t, S>(a.src, me.elem(i));
+    T Fx, Fy, Fz;
+    load_force<T>(a.P, a.P.field ? a.tb.fbase[t] : 0, rec.mask, Fx, Fy, Fz);
+    macro_node(a.P, (double)Fx, (double)Fy, (double)Fz,
+               [&](int i) { return (double)C::dec(raw[i], a.P.inv_scale); }, rho, ux, uy, uz);
+}
+
+// tile after tile, for boxes of mostly dropped tiles: the sums, and the
+// fluid nodes of the fields asked for
+template <int ST>
+__global__ __launch_bounds__(MACRO_THREADS) void k_sums(KArgs a, int nx, int ny, int nz, double *rho_out,
+                                                        double *u_out, double *partials) {
     const int lane = (int)(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int waves = (int)gridDim.x * (MACRO_THREADS / 64);
+    const size_t N = (size_t)nx * ny * nz;
     MacroSums sums;
     int t = (int)blockIdx.x * (MACRO_THREADS / 64) + wave;
     TileRec ahead = t < a.n_tiles ? a.tb.rec[t] : TileRec{0, 0};
@@ -1425,58 +1456,95 @@ __global__ __launch_bounds__(MACRO_THREADS) void k_sums(KArgs a, double *partial
         const TileRec rec = ahead;
         ahead = t + waves < a.n_tiles ? a.tb.rec[t + waves] : TileRec{0, 0};
         if (!((rec.mask >> lane) & 1)) continue;
-        const Self<C::RUNS, uint64_t> me(rec, lane);
-        S raw[Q];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) raw[i] = load_elem<uint64_t, S>(a.src, me.elem(i));
-        T Fx, Fy, Fz;
-        load_force<T>(a.P, a.P.field ? a.tb.fbase[t] : 0, rec.mask, Fx, Fy, Fz);
         double rho, ux, uy, uz;
-        macro_node(a.P, (double)Fx, (double)Fy, (double)Fz,
-                   [&](int i) { return (double)C::dec(raw[i], a.P.inv_scale); }, rho, ux, uy, uz);
+        macro_of_tile<ST>(a, t, rec, lane, rho, ux, uy, uz);
         sums.add(rho, ux, uy, uz);
+        if (rho_out || u_out) {
+            const size_t at = dense_index(a.tb.xyz + 4 * (size_t)t, lane, nx, ny);
+            if (rho_out) rho_out[at] = rho;
+            if (u_out) {
+                u_out[at] = ux;
+                u_out[N + at] = uy;
+                u_out[2 * N + at] = uz;
+            }
+        }
     }
     sums.store(partials);
 }
 
-// the fields, and with SUMS the sums of the same pass
-template <int ST, bool SUMS>
+// tables that are read through the scalar unit in a loop that stores: a vector
+// load would be waited for with every store issued before it
+template <typename T>
+using Uniform = const __attribute__((address_space(4))) T *;
+
+// A walk of the box, wave w on tile w of a group, lane n on its node n: the
+// sums, and with FIELDS the fields asked for.  These pass
+// through LDS into rows of 16 nodes along x, which makes a store of a wave 4
+// whole lines; the loads are a tile's whole blocks, and the sums are the same
+// additions in the same order whether the fields are written or not.  Bound by
+// memory, with a group's latencies covered by 8 workgroups per CU (256^3 pack,
+// FP64 / FP32 / FP16, us a call: fields 350 / 250 / 229, where lanes laid along
+// the rows for the loads as well took 373 / 271 / 260; sums alone 219 / 134 /
+// 128, of which the groups' dropped tiles take 10 / 13 / 29).
+template <int ST, bool FIELDS>
 __global__ __launch_bounds__(MACRO_THREADS) void k_fields(KArgs a, DenseBox b, int groups, double *rho_out,
                                                           double *u_out, double *partials) {
-    using C = Codec<ST>;
-    using S = typename C::S;
-    using T = typename C::T;
+    const int lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const size_t N = (size_t)b.nx * b.ny * b.nz;
+    __shared__ double rows[FIELDS ? 2 : 1][4][FIELDS ? MACRO_THREADS : 1];
+    int buf = 0;
     MacroSums sums;
-    for (DenseWalk w(a.tb, b, groups); w.more();) {
-        const DenseNode d = w.next();
-        double rho = 0, ux = 0, uy = 0, uz = 0;
-        if (d.fl) {
-            S raw[Q];
+    const Uniform<int32_t> map = (Uniform<int32_t>)b.map;
+    const Uniform<TileRec> recs = (Uniform<TileRec>)a.tb.rec;
+    // the wave's tile of group i, or -1
+    const auto lookup = [&](int i) {
+        if (i >= groups) return -1;
+        const int gr = remap_block(i, groups, DENSE_LC);
+        const int row = gr / b.gx, tx = 4 * (gr - row * b.gx) + wave;
+        return tx < b.tx ? map[(size_t)row * b.tx + tx] : -1;
+    };
+    const auto mask_of = [&](int t) { return t >= 0 ? recs[t].mask : 0ull; };
+    const auto base_of = [&](int t) { return t >= 0 ? recs[t].base : 0ull; };
+    // a tile's record is loaded one group ahead, its number two
+    int g = (int)blockIdx.x;
+    int t = lookup(g), t1 = lookup(g + (int)gridDim.x);
+    uint64_t mask = mask_of(t), base = base_of(t);
+    for (; g < groups; g += (int)gridDim.x) {
+        const int t2 = lookup(g + 2 * (int)gridDim.x);
+        const uint64_t mask1 = mask_of(t1), base1 = base_of(t1);
+        double v[4] = {0.0, 0.0, 0.0, 0.0};  // rho, u
+        if (lane_on(mask)) {
+            macro_of_tile<ST>(a, t, TileRec{mask, base}, lane, v[0], v[1], v[2], v[3]);
+            sums.add(v[0], v[1], v[2], v[3]);
+        }
+        if constexpr (FIELDS) {
+            const int gr = remap_block(g, groups, DENSE_LC);
+            const int row = gr / b.gx, gx = gr - row * b.gx;
+            const int tz = row / b.ty, ty = row - tz * b.ty;
+            const int to = (lane >> 4) * 64 + (lane >> 2 & 3) * 16 + 4 * wave + (lane & 3);
 #pragma unroll
-            for (int i = 0; i < Q; ++i) raw[i] = load_elem<uint64_t, S>(a.src, d.template elem<C::RUNS>(i));
-            T Fx = T(a.P.F[0]), Fy = T(a.P.F[1]), Fz = T(a.P.F[2]);
-            if (a.P.field) {
-                const T *f = reinterpret_cast<const T *>(a.P.field);
-                const uint64_t first = a.tb.fbase[d.tile];
-                Fx = f[d.field_entry(first, 0)];
-                Fy = f[d.field_entry(first, 1)];
-                Fz = f[d.field_entry(first, 2)];
-            }
-            macro_node(a.P, (double)Fx, (double)Fy, (double)Fz,
-                       [&](int i) { return (double)C::dec(raw[i], a.P.inv_scale); }, rho, ux, uy, uz);
-            if constexpr (SUMS) sums.add(rho, ux, uy, uz);
-        }
-        if (d.in) {
-            if (rho_out) rho_out[d.at] = rho;
-            if (u_out) {
-                u_out[d.at] = ux;
-                u_out[N + d.at] = uy;
-                u_out[2 * N + d.at] = uz;
+            for (int c = 0; c < 4; ++c) rows[buf][c][to] = v[c];
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = rows[buf][c][threadIdx.x];
+            buf ^= 1;  // the next barrier comes before this half is written again
+            const int X = 16 * gx + (lane & 15), Y = 4 * ty + (lane >> 4), Z = 4 * tz + wave;
+            if (X < b.nx && Y < b.ny && Z < b.nz) {
+                const size_t at = (size_t)X + (size_t)b.nx * ((size_t)Y + (size_t)b.ny * (size_t)Z);
+                if (rho_out) rho_out[at] = v[0];
+                if (u_out) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) u_out[c * N + at] = v[1 + c];
+                }
             }
         }
+        t = t1;
+        t1 = t2;
+        mask = mask1;
+        base = base1;
     }
-    if constexpr (SUMS) sums.store(partials);
+    sums.store(partials);
 }
 
 // one workgroup reduces the rows of partial sums in a fixed order: thread t
@@ -1486,13 +1554,14 @@ constexpr int RED_THREADS = 64 * NSUM;
 __global__ __launch_bounds__(RED_THREADS) void k_reduce(const double *partials, int rows, double *out) {
     __shared__ double sh[RED_THREADS];
     const int tid = (int)threadIdx.x, c = tid % NSUM;
-    double acc = 0.0;
+    double acc = 0.0, kept = 0.0, most = 0.0;  // the sum and the maximum, of which a column takes one
 #pragma unroll 8
     for (int j = tid; j < rows * NSUM; j += RED_THREADS) {
         const double v = partials[j];
-        acc = (c == 5) ? fmax(acc, v) : acc + v;
+        add_kept(acc, kept, v);
+        most = fmax(most, v);
     }
-    sh[tid] = acc;
+    sh[tid] = c == 5 ? most : kept_total(acc, kept);
     __syncthreads();
     for (int s = RED_THREADS / 2; s >= NSUM; s >>= 1) {
         if (tid < s) sh[tid] = (c == 5) ? fmax(sh[tid], sh[tid + s]) : sh[tid] + sh[tid + s];
@@ -2177,40 +2246,48 @@ static int dense_groups(const DenseBox &b) {
     return g <= INT32_MAX ? (int)g : -1;
 }
 
-// Workgroups of a pass that walks the tiles or the box in strides: all that
-// are resident at once (2048 of 4 waves, 8 waves per SIMD), and 4 times that
-// for the fields, whose walk gains from it (256^3 pack: 378 us a call against
-// 392 with 2048 and 470 with one workgroup per group).  A summing pass has at
-// most one workgroup per tile, for which there are rows of partial sums.
-constexpr int SUM_GROUPS = 2048;
-constexpr int FIELD_GROUPS = 8192;
+// Whether a pass over a dense array walks the box, or takes its kept tiles one
+// by one after the array has been cleared: it walks up to four groups of four
+// tiles per kept tile.  A 384^3 box, FP64, us walked and tile by tile: with 6%
+// of its tiles kept (4.2 groups per kept tile) all fields 516 and 624, one
+// field 299 and 263, the sums alone 138 and 102; with 3% (8.4) 469 and 500, 284 and 191,
+// 124 and 56.
+static bool walks_box(const Launch &L, int groups) { return groups <= (int64_t)4 * L.n_tiles; }
 
+// Workgroups of a pass that goes over the tiles or the box in strides: 2048 of
+// 4 waves, about as many as are resident at once, and 4 times that for the
+// fields and sums of a large box (256^3 pack, FP64, us a call for the
+// fields: 348 with 8192, 375 with 2048; 192^3 267 and 264; 128^3 68 and 57.5, every
+// workgroup leaving a row to be added up).
+constexpr int WALK_GROUPS = 2048;
+constexpr int MACRO_GROUPS = 8192;
+
+// The way over the box, and so the order of the additions, follows from the
+// tiles and the box alone: a call with fields and one without return the same
+// sums bit by bit.  A summing pass has at most one workgroup per tile, for
+// which there are rows of partial sums.
 template <int ST>
 static hipError_t macro_t(const Launch &L, const KArgs &a, double *rho, double *u, int nx, int ny, int nz,
                           double *partials, int *rows) {
     const DenseBox b = dense_box(L, nx, ny, nz);
     const int groups = dense_groups(b);
     if (groups < 0) return hipErrorInvalidValue;
-    const bool fields = rho || u;
-    // with fewer tiles than that, a box may be large and nearly empty: its
-    // fields are written by a pass of their own, with a full launch
-    const bool fused = fields && L.n_tiles >= SUM_GROUPS;
-    if (fields) {
-        int grid = groups < FIELD_GROUPS ? groups : FIELD_GROUPS;
-        if (fused && grid > L.n_tiles) grid = L.n_tiles;
-        if (fused)
-            hipLaunchKernelGGL((k_fields<ST, true>), dim3(grid), dim3(MACRO_THREADS), 0, L.stream, a, b, groups, rho, u,
-                               partials);
-        else
-            hipLaunchKernelGGL((k_fields<ST, false>), dim3(grid), dim3(MACRO_THREADS), 0, L.stream, a, b, groups, rho,
-                               u, partials);
+    if (walks_box(L, groups)) {
+        int grid = groups < 4 * MACRO_GROUPS ? WALK_GROUPS : MACRO_GROUPS;
+        if (grid > groups) grid = groups;
+        if (grid > L.n_tiles) grid = L.n_tiles;
+        const auto fn = rho || u ? k_fields<ST, true> : k_fields<ST, false>;
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(MACRO_THREADS), 0, L.stream, a, b, groups, rho, u, partials);
         *rows = grid;
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess || fused) return e;
+        return hipGetLastError();
     }
+    const size_t N = (size_t)nx * ny * nz;
+    hipError_t e = rho ? launch_fill(L.stream, rho, N) : hipSuccess;
+    if (e == hipSuccess && u) e = launch_fill(L.stream, u, 3 * N);
+    if (e != hipSuccess) return e;
     const int waves = MACRO_THREADS / 64, tiles = (L.n_tiles + waves - 1) / waves;
-    const int grid = tiles < SUM_GROUPS ? tiles : SUM_GROUPS;
-    hipLaunchKernelGGL(k_sums<ST>, dim3(grid), dim3(MACRO_THREADS), 0, L.stream, a, partials);
+    const int grid = tiles < WALK_GROUPS ? tiles : WALK_GROUPS;
+    hipLaunchKernelGGL(k_sums<ST>, dim3(grid), dim3(MACRO_THREADS), 0, L.stream, a, nx, ny, nz, rho, u, partials);
     *rows = grid;
     return hipGetLastError();
 }
@@ -2243,7 +2320,7 @@ static hipError_t dense_walk(const Launch &L, K kernel, const KArgs &a, int nx, 
     const DenseBox b = dense_box(L, nx, ny, nz);
     const int groups = dense_groups(b);
     if (groups < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kernel, dim3(groups < SUM_GROUPS ? groups : SUM_GROUPS), dim3(256), 0, L.stream, a, b, groups,
+    hipLaunchKernelGGL(kernel, dim3(groups < WALK_GROUPS ? groups : WALK_GROUPS), dim3(256), 0, L.stream, a, b, groups,
                        args...);
     return hipGetLastError();
 }
