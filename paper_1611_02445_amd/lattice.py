@@ -130,13 +130,6 @@ class Lattice:
             destroy(ctx)
             self.ctx = None
 
-    def _keep(self, t):
-        """t, which may be a conversion of the caller's tensor, has to live until the lattice's stream has
-        read it.  On the current stream its memory is not handed out again before that; on any other the
-        stream is waited for."""
-        if self.torch.cuda.current_stream(self.device) != self.stream:
-            self.stream.synchronize()
-
     # -- sizes ---------------------------------------------------------------
     @property
     def n_tiles(self):
@@ -250,7 +243,8 @@ class Lattice:
         if tuple(f.shape) != (19,) + self.dense_shape:
             raise ValueError(f"state must have shape {(19,) + self.dense_shape}")
         call("lbm_set_state", self.ctx, _vp(f), _vp(state))
-        self._keep(f)
+        # the caller's tensor may be freed or overwritten on any stream once this returns
+        self.stream.synchronize()
 
     def field_to_dense(self, field_buf, dtype=0):
         """A per-node field (force density, force gradient) as a dense FP64
@@ -289,7 +283,7 @@ class Lattice:
         if tuple(v.shape) != (19,) + self.dense_shape:
             raise ValueError(f"adjoint lattice must have shape {(19,) + self.dense_shape}")
         call("lbm_adjoint_set", self.ctx, _vp(v), _vp(adj))
-        self._keep(v)
+        self.stream.synchronize()  # as set_state
 
     def info(self):
         n_t, n_f, st, gb = ctypes.c_int32(), ctypes.c_int64(), ctypes.c_int32(), ctypes.c_int32()
