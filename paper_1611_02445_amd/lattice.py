@@ -130,6 +130,19 @@ class Lattice:
             destroy(ctx)
             self.ctx = None
 
+    def _dense(self, x, shape, what):
+        """x as a contiguous FP64 device tensor that the lattice's stream may read: a conversion runs on the
+        current stream, which comes before what the lattice's stream does next."""
+        torch = self.torch
+        given = torch.as_tensor(x)
+        t = given.to(device=self.device, dtype=torch.float64).contiguous()
+        if tuple(t.shape) != shape:
+            raise ValueError(f"{what} must have shape {shape}")
+        current = torch.cuda.current_stream(self.device)
+        if t is not given and current != self.stream:
+            self.stream.wait_stream(current)
+        return t
+
     # -- sizes ---------------------------------------------------------------
     @property
     def n_tiles(self):
@@ -163,12 +176,12 @@ class Lattice:
         [3, nz, ny, nx] on the device (per node)."""
         torch = self.torch
         if isinstance(g, torch.Tensor):
-            g = g.to(device=self.device, dtype=torch.float64).contiguous()
-            if tuple(g.shape) != (3,) + self.dense_shape:
-                raise ValueError(f"force field must have shape {(3,) + self.dense_shape}")
+            g = self._dense(g, (3,) + self.dense_shape, "force field")
             if self.force_buf is None:
                 self.force_buf = torch.empty(max(self.sizes.force_bytes, 1), dtype=torch.uint8, device=self.device)
             call("lbm_set_force", self.ctx, 0.0, 0.0, 0.0, _vp(g), _vp(self.force_buf))
+            if torch.cuda.current_stream(self.device) != self.stream:
+                g.record_stream(self.stream)
             self._force_src = g
         else:
             gx, gy, gz = map(float, g)
@@ -238,10 +251,7 @@ class Lattice:
         return out
 
     def set_state(self, f_dense, state=None):
-        torch = self.torch
-        f = torch.as_tensor(f_dense).to(device=self.device, dtype=torch.float64).contiguous()
-        if tuple(f.shape) != (19,) + self.dense_shape:
-            raise ValueError(f"state must have shape {(19,) + self.dense_shape}")
+        f = self._dense(f_dense, (19,) + self.dense_shape, "state")
         call("lbm_set_state", self.ctx, _vp(f), _vp(state))
         # the caller's tensor may be freed or overwritten on any stream once this returns
         self.stream.synchronize()
@@ -278,10 +288,7 @@ class Lattice:
         return out
 
     def adjoint_set(self, dense, adj):
-        torch = self.torch
-        v = torch.as_tensor(dense).to(device=self.device, dtype=torch.float64).contiguous()
-        if tuple(v.shape) != (19,) + self.dense_shape:
-            raise ValueError(f"adjoint lattice must have shape {(19,) + self.dense_shape}")
+        v = self._dense(dense, (19,) + self.dense_shape, "adjoint lattice")
         call("lbm_adjoint_set", self.ctx, _vp(v), _vp(adj))
         self.stream.synchronize()  # as set_state
 
