@@ -348,8 +348,12 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
 
     // without it the sums are copied out of the scratch
     void *pinned = nullptr;
-    if (n > 0 && c->device >= 0 && hipHostMalloc(&pinned, NSUM * sizeof(double), hipHostMallocDefault) == hipSuccess)
-        c->host_sums = reinterpret_cast<double *>(pinned);
+    if (n > 0 && c->device >= 0) {
+        if (hipHostMalloc(&pinned, NSUM * sizeof(double), hipHostMallocDefault) == hipSuccess)
+            c->host_sums = reinterpret_cast<double *>(pinned);
+        else
+            (void)hipGetLastError();  // or the next launch reports it as its own
+    }
 
     // every byte offset into a lattice (an adjoint lattice has the layout and
     // size of the state) must fit 32 bits for the 32-bit kernels; the others
