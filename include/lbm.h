@@ -29,8 +29,10 @@
  *     16 entries, tiles in device order; lbm_field_to_dense converts;
  *   - device pointers are plain HIP device addresses owned by the caller; the
  *     library allocates no device buffers (lbm_step_graphed alone creates a
- *     private stream and executable graphs, and lbm_create one pinned host
- *     block of 64 bytes, held by the context until lbm_destroy);
+ *     private stream and executable graphs, held by the context until
+ *     lbm_destroy; the first lbm_create of the process allocates one pinned
+ *     host block of 4 KB, kept to its end, of which a context has 64 bytes
+ *     while it lives);
  *   - a context is not thread-safe: one host thread at a time may call into
  *     it; distinct contexts are independent;
  *   - every call returns an lbm_status; on failure lbm_last_error() gives a

@@ -53,13 +53,56 @@ struct lbm_ctx {
     double *noalloc = nullptr;      // this device's copy of noalloc_scratch (lbm_macroscopic_noalloc)
     hipError_t noalloc_err = hipSuccess;
     double *host_sums = nullptr;    // pinned: the reduced sums of a macroscopic call, written by the kernel
-    ~lbm_ctx() {
-        if (host_sums) (void)hipHostFree(host_sums);
-        graphs[0].release();
-        graphs[1].release();
-        if (capture) (void)hipStreamDestroy(capture);
-    }
+    ~lbm_ctx();
 };
+
+// Pinned rows for the sums of SUM_ROWS contexts at a time, in one block of the
+// process that is allocated with its first context.  It is never freed:
+// hipHostFree waits for every stream of the device, so a context that freed
+// memory of its own would make lbm_destroy wait for the others' work.
+namespace {
+constexpr int SUM_ROWS = 64;
+std::mutex sum_rows_mutex;
+double *sum_rows;
+uint64_t sum_rows_taken;
+
+// a row that no other context has, or null: the caller then does without
+double *take_sum_row() {
+    std::lock_guard<std::mutex> lock(sum_rows_mutex);
+    if (!sum_rows) {
+        // allowed while another thread captures a graph, which it has no part in
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, SUM_ROWS * NSUM * sizeof(double), hipHostMallocPortable) == hipSuccess)
+            sum_rows = reinterpret_cast<double *>(p);
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (!sum_rows) {
+            (void)hipGetLastError();  // or the next launch reports it as its own
+            return nullptr;
+        }
+    }
+    for (int i = 0; i < SUM_ROWS; ++i)
+        if (!(sum_rows_taken >> i & 1)) {
+            sum_rows_taken |= 1ull << i;
+            return sum_rows + i * NSUM;
+        }
+    return nullptr;
+}
+
+void give_sum_row(const double *row) {
+    if (!row) return;
+    std::lock_guard<std::mutex> lock(sum_rows_mutex);
+    sum_rows_taken &= ~(1ull << (row - sum_rows) / NSUM);
+}
+}  // namespace
+
+lbm_ctx::~lbm_ctx() {
+    give_sum_row(host_sums);
+    graphs[0].release();
+    graphs[1].release();
+    if (capture) (void)hipStreamDestroy(capture);
+}
 
 namespace {
 
@@ -347,13 +390,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     c->noalloc_err = c->device >= 0 ? noalloc_lookup(c->device, &c->noalloc) : hipErrorNoDevice;
 
     // without it the sums are copied out of the scratch
-    void *pinned = nullptr;
-    if (n > 0 && c->device >= 0) {
-        if (hipHostMalloc(&pinned, NSUM * sizeof(double), hipHostMallocDefault) == hipSuccess)
-            c->host_sums = reinterpret_cast<double *>(pinned);
-        else
-            (void)hipGetLastError();  // or the next launch reports it as its own
-    }
+    if (n > 0 && c->device >= 0) c->host_sums = take_sum_row();
 
     // every byte offset into a lattice (an adjoint lattice has the layout and
     // size of the state) must fit 32 bits for the 32-bit kernels; the others
@@ -689,7 +726,10 @@ static int macroscopic_into(lbm_ctx *c, const void *state, double *rho_dev, doub
     if (e == hipSuccess && !c->host_sums)
         e = hipMemcpyAsync(sums, final_, NSUM * sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return hip_fail(e, "lbm_macroscopic");
+    if (e != hipSuccess) {
+        c->host_sums = nullptr;  // not given back: a kernel may yet write there
+        return hip_fail(e, "lbm_macroscopic");
+    }
     if (c->host_sums) std::memcpy(sums, c->host_sums, NSUM * sizeof(double));
     return check_sums(c, sums, "lbm_macroscopic");
 }
