@@ -1292,6 +1292,7 @@ struct DenseNode {
 // whole rows (256^3 pack, fields and sums: 378 us a call, 382 without the
 // re-numbering, 387 with chunks of 64).
 constexpr int DENSE_LC = 4;
+constexpr int WALK_LW = 2;  // 4 waves in a workgroup
 struct DenseWalk {
     const DevTables &tb;
     const DenseBox &b;
@@ -1334,6 +1335,32 @@ struct DenseWalk {
         rec0 = record(tile1);
         tile1 = lookup(g + 2 * (int)gridDim.x);
         g += (int)gridDim.x;
+        return d;
+    }
+};
+
+// The kept tiles alone, one for each wave, for an array that has been cleared:
+// nodes that are not fluid count as outside.
+struct TileWalk {
+    const DevTables &tb;
+    const DenseBox &b;
+    const int n_tiles;
+    int t;
+    __device__ __forceinline__ TileWalk(const DevTables &tb_, const DenseBox &b_, int n_tiles_)
+        : tb(tb_), b(b_), n_tiles(n_tiles_), t(wave_tile(WALK_LW, (int)gridDim.x)) {}
+    __device__ __forceinline__ bool more() const { return t < n_tiles; }
+    __device__ __forceinline__ DenseNode next() {
+        const int lane = (int)(threadIdx.x & 63);
+        const TileRec rec = tb.rec[t];
+        DenseNode d;
+        d.in = d.fl = (rec.mask >> lane) & 1;
+        d.tile = t;
+        d.n = lane;
+        d.base = rec.base;
+        d.k = __builtin_popcountll(rec.mask);
+        d.rank = mbcnt(rec.mask);
+        d.at = dense_index(tb.xyz + 4 * (size_t)t, lane, b.nx, b.ny);
+        t = n_tiles;
         return d;
     }
 };
@@ -1573,12 +1600,12 @@ __global__ __launch_bounds__(RED_THREADS) void k_reduce(const double *partials, 
 // ---------------------------------------------------------------------------
 // dense <-> tile conversions
 // ---------------------------------------------------------------------------
-template <int ST>
-__global__ __launch_bounds__(256) void k_get_state(KArgs a, DenseBox b, int groups, double *dense) {
+template <class Walk, int ST>
+__global__ __launch_bounds__(64 << WALK_LW) void k_get_state(KArgs a, DenseBox b, int groups, double *dense) {
     using C = Codec<ST>;
     using S = typename C::S;
     const size_t N = (size_t)b.nx * b.ny * b.nz;
-    for (DenseWalk w(a.tb, b, groups); w.more();) {
+    for (Walk w(a.tb, b, groups); w.more();) {
         const DenseNode d = w.next();
         S raw[Q];
         if (d.fl) {
@@ -1645,10 +1672,10 @@ __global__ __launch_bounds__(512) void k_force_to_tiles(KArgs a, const double *g
 }
 
 // per-fluid-slot field [3 components] -> dense FP64 [3][nz][ny][nx]
-template <typename T>
-__global__ __launch_bounds__(256) void k_field_to_dense(KArgs a, DenseBox b, int groups, const T *in, double *dense) {
+template <class Walk, typename T>
+__global__ __launch_bounds__(64 << WALK_LW) void k_field_to_dense(KArgs a, DenseBox b, int groups, const T *in, double *dense) {
     const size_t N = (size_t)b.nx * b.ny * b.nz;
-    for (DenseWalk w(a.tb, b, groups); w.more();) {
+    for (Walk w(a.tb, b, groups); w.more();) {
         const DenseNode d = w.next();
         T v[3] = {T(0), T(0), T(0)};
         if (d.fl) {
@@ -1662,10 +1689,11 @@ __global__ __launch_bounds__(256) void k_field_to_dense(KArgs a, DenseBox b, int
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_tiles_to_dense(KArgs a, DenseBox b, int groups, const T *in, int ncomp, double *dense) {
+template <class Walk, typename T>
+__global__ __launch_bounds__(64 << WALK_LW) void k_tiles_to_dense(KArgs a, DenseBox b, int groups, const T *in, int ncomp,
+                                                                  double *dense) {
     const size_t N = (size_t)b.nx * b.ny * b.nz;
-    for (DenseWalk w(a.tb, b, groups); w.more();) {
+    for (Walk w(a.tb, b, groups); w.more();) {
         const DenseNode d = w.next();
         if (!d.in) continue;
         for (int c = 0; c < ncomp; ++c)
@@ -2247,12 +2275,16 @@ static int dense_groups(const DenseBox &b) {
 }
 
 // Whether a pass over a dense array walks the box, or takes its kept tiles one
-// by one after the array has been cleared: it walks up to four groups of four
-// tiles per kept tile.  A 384^3 box, FP64, us walked and tile by tile: with 6%
-// of its tiles kept (4.2 groups per kept tile) all fields 516 and 624, one
-// field 299 and 263, the sums alone 138 and 102; with 3% (8.4) 469 and 500, 284 and 191,
-// 124 and 56.
-static bool walks_box(const Launch &L, int groups) { return groups <= (int64_t)4 * L.n_tiles; }
+// by one after the array has been cleared: it walks up to two groups of four
+// tiles per kept tile.  A 384^3 box, FP64, us walked and tile by tile:
+//   kept tiles (groups per kept tile)  all fields  sums alone   lattice    per-node field
+//   one 170 x 170 duct (1.2)            755   864   313   290  2271  2415   390   378
+//   15% scattered (1.7)                 668   983   251   226  2780  3338   475   560
+//   10% scattered (2.5)                 582   787   178   157  2635  2790   446   473
+//   one 120 x 120 duct (2.6)            582   601   179   154  2040  1975   355   309
+//   6% scattered (4.2)                  516   624   138   102  2305  2327   413   401
+//   one 64 x 64 duct (9)                456   421   119    53  1907  1663   341   259
+static bool walks_box(const Launch &L, int groups) { return groups <= (int64_t)2 * L.n_tiles; }
 
 // Workgroups of a pass that goes over the tiles or the box in strides: 2048 of
 // 4 waves, about as many as are resident at once, and 4 times that for the
@@ -2311,27 +2343,52 @@ hipError_t launch_reduce(hipStream_t s, const double *partials, int rows, double
     return hipGetLastError();
 }
 
-// runs a kernel of the dense walk, or clears `out` where no tile is kept (the
-// tables are then absent)
+// runs a kernel over the box, or clears `out` and runs it over the kept tiles
+// (without one the tables are absent)
 template <class K, class... Args>
-static hipError_t dense_walk(const Launch &L, K kernel, const KArgs &a, int nx, int ny, int nz, size_t out_elems,
-                             double *out, Args... args) {
-    if (L.n_tiles == 0) return launch_fill(L.stream, out, out_elems);
+static hipError_t to_dense(const Launch &L, K by_box, K by_tile, const KArgs &a, int nx, int ny, int nz,
+                           size_t out_elems, double *out, Args... args) {
     const DenseBox b = dense_box(L, nx, ny, nz);
     const int groups = dense_groups(b);
     if (groups < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kernel, dim3(groups < WALK_GROUPS ? groups : WALK_GROUPS), dim3(256), 0, L.stream, a, b, groups,
-                       args...);
+    const int threads = 64 << WALK_LW;
+    if (walks_box(L, groups)) {
+        hipLaunchKernelGGL(by_box, dim3(groups < WALK_GROUPS ? groups : WALK_GROUPS), dim3(threads), 0, L.stream, a, b,
+                           groups, args...);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_fill(L.stream, out, out_elems);
+    if (e != hipSuccess || L.n_tiles == 0) return e;
+    const int grid = (L.n_tiles + (1 << WALK_LW) - 1) >> WALK_LW;
+    hipLaunchKernelGGL(by_tile, dim3(grid), dim3(threads), 0, L.stream, a, b, L.n_tiles, args...);
     return hipGetLastError();
+}
+
+template <int ST>
+static hipError_t get_state_t(const Launch &L, const KArgs &a, double *dense, int nx, int ny, int nz) {
+    return to_dense(L, k_get_state<DenseWalk, ST>, k_get_state<TileWalk, ST>, a, nx, ny, nz,
+                    (size_t)Q * nx * ny * nz, dense, dense);
+}
+
+template <typename T>
+static hipError_t field_t(const Launch &L, const KArgs &a, const void *field, double *dense, int nx, int ny, int nz) {
+    return to_dense(L, k_field_to_dense<DenseWalk, T>, k_field_to_dense<TileWalk, T>, a, nx, ny, nz,
+                    (size_t)3 * nx * ny * nz, dense, reinterpret_cast<const T *>(field), dense);
+}
+
+template <typename T>
+static hipError_t tiles_t(const Launch &L, const KArgs &a, const void *buf, int ncomp, double *dense, int nx, int ny,
+                          int nz) {
+    return to_dense(L, k_tiles_to_dense<DenseWalk, T>, k_tiles_to_dense<TileWalk, T>, a, nx, ny, nz,
+                    (size_t)ncomp * nx * ny * nz, dense, reinterpret_cast<const T *>(buf), ncomp, dense);
 }
 
 hipError_t launch_get_state(const Launch &L, const Phys &P, const void *state, double *dense, int nx, int ny, int nz) {
     const KArgs a = make_args(L, P, state, nullptr);
-    const size_t n = (size_t)Q * nx * ny * nz;
     switch (P.storage) {
-    case LBM_F64: return dense_walk(L, k_get_state<LBM_F64>, a, nx, ny, nz, n, dense, dense);
-    case LBM_F32: return dense_walk(L, k_get_state<LBM_F32>, a, nx, ny, nz, n, dense, dense);
-    default: return dense_walk(L, k_get_state<LBM_F16S>, a, nx, ny, nz, n, dense, dense);
+    case LBM_F64: return get_state_t<LBM_F64>(L, a, dense, nx, ny, nz);
+    case LBM_F32: return get_state_t<LBM_F32>(L, a, dense, nx, ny, nz);
+    default: return get_state_t<LBM_F16S>(L, a, dense, nx, ny, nz);
     }
 }
 
@@ -2362,24 +2419,15 @@ hipError_t launch_field_to_dense(const Launch &L, const void *field, int dtype, 
                                  int nz) {
     Phys P{};
     const KArgs a = make_args(L, P, nullptr, nullptr);
-    const size_t n = (size_t)3 * nx * ny * nz;
-    if (dtype == 0)
-        return dense_walk(L, k_field_to_dense<double>, a, nx, ny, nz, n, dense, reinterpret_cast<const double *>(field),
-                          dense);
-    return dense_walk(L, k_field_to_dense<float>, a, nx, ny, nz, n, dense, reinterpret_cast<const float *>(field),
-                      dense);
+    return dtype == 0 ? field_t<double>(L, a, field, dense, nx, ny, nz) : field_t<float>(L, a, field, dense, nx, ny, nz);
 }
 
 hipError_t launch_tiles_to_dense(const Launch &L, const void *tile_buf, int ncomp, int dtype, double *dense, int nx,
                                  int ny, int nz) {
     Phys P{};
     const KArgs a = make_args(L, P, nullptr, nullptr);
-    const size_t n = (size_t)ncomp * nx * ny * nz;
-    if (dtype == 0)
-        return dense_walk(L, k_tiles_to_dense<double>, a, nx, ny, nz, n, dense,
-                          reinterpret_cast<const double *>(tile_buf), ncomp, dense);
-    return dense_walk(L, k_tiles_to_dense<float>, a, nx, ny, nz, n, dense, reinterpret_cast<const float *>(tile_buf),
-                      ncomp, dense);
+    return dtype == 0 ? tiles_t<double>(L, a, tile_buf, ncomp, dense, nx, ny, nz)
+                      : tiles_t<float>(L, a, tile_buf, ncomp, dense, nx, ny, nz);
 }
 
 // the adjoint kernels exist for FP64 and FP32 storage (runs layout) and every
