@@ -1262,10 +1262,27 @@ __device__ __forceinline__ double wave_max(double v) {
 // tiles that were dropped are written too, so no pass over the array clears it
 // first, and a read of a lattice block is the 16 consecutive slots of each of
 // the 4 tiles' planes.
+// In a box of one tile along x the group is 4 tiles along y, whose planes are 64
+// consecutive nodes: lane l is node (l & 3, l >> 2), in tile l >> 4.
 struct DenseBox {
     const int32_t *map;  // [tz][ty][tx] device tile number, -1 for a dropped tile
-    int tx, ty, gx;      // tiles along x and y, workgroups along x
+    int tx, ty, gx;      // tiles along the group's axis and (along x) the next one, groups along the axis
     int nx, ny, nz;
+    bool along_y;
+    // tile of the group, and y in it or (along y) in the group, of a lane of a plane
+    __device__ __forceinline__ int tile_of(int lane) const { return lane >> (along_y ? 4 : 2) & 3; }
+    __device__ __forceinline__ int y_of(int lane) const { return lane >> (along_y ? 2 : 4); }
+    // the node of plane z of group (gx, row), and whether the box has it
+    struct At {
+        size_t at;
+        bool in;
+    };
+    __device__ __forceinline__ At node(int gx, int row, int lane, int z) const {
+        const int tz = row / ty, t = row - tz * ty;
+        const int X = along_y ? lane & 3 : 16 * gx + (lane & 15), Y = (along_y ? 16 * gx : 4 * t) + y_of(lane);
+        const int Z = 4 * tz + z;
+        return At{(size_t)X + (size_t)nx * ((size_t)Y + (size_t)ny * (size_t)Z), X < nx && Y < ny && Z < nz};
+    }
 };
 
 struct DenseNode {
@@ -1310,7 +1327,7 @@ struct DenseWalk {
     __device__ __forceinline__ int lookup(int i) const {
         if (i >= groups) return -1;
         const int gr = remap_block(i, groups, DENSE_LC);
-        const int row = gr / b.gx, tx = 4 * (gr - row * b.gx) + (int)(threadIdx.x >> 2 & 3);
+        const int row = gr / b.gx, tx = 4 * (gr - row * b.gx) + b.tile_of((int)(threadIdx.x & 63));
         return tx < b.tx ? b.map[(size_t)row * b.tx + tx] : -1;
     }
     __device__ __forceinline__ TileRec record(int t) const { return t >= 0 ? tb.rec[t] : TileRec{0, 0}; }
@@ -1320,12 +1337,10 @@ struct DenseWalk {
         const int lane = (int)(threadIdx.x & 63), z = (int)(threadIdx.x >> 6);
         const int gr = remap_block(g, groups, DENSE_LC);
         const int row = gr / b.gx, gx = gr - row * b.gx;
-        const int tz = row / b.ty, ty = row - tz * b.ty;
-        const int x16 = lane & 15, y = lane >> 4;
-        const int X = 16 * gx + x16, Y = 4 * ty + y, Z = 4 * tz + z;
-        d.in = X < b.nx && Y < b.ny && Z < b.nz;
-        d.at = (size_t)X + (size_t)b.nx * ((size_t)Y + (size_t)b.ny * (size_t)Z);
-        d.n = (x16 & 3) + 4 * y + 16 * z;
+        const DenseBox::At at = b.node(gx, row, lane, z);
+        d.in = at.in;
+        d.at = at.at;
+        d.n = (lane & 3) + 4 * (b.y_of(lane) & 3) + 16 * z;
         d.tile = tile0;
         d.base = rec0.base;
         d.fl = (rec0.mask >> d.n) & 1;
@@ -1547,22 +1562,22 @@ __global__ __launch_bounds__(MACRO_THREADS) void k_fields(KArgs a, DenseBox b, i
         }
         if constexpr (FIELDS) {
             const int gr = remap_block(g, groups, DENSE_LC);
-            const int row = gr / b.gx, gx = gr - row * b.gx;
-            const int tz = row / b.ty, ty = row - tz * b.ty;
-            const int to = (lane >> 4) * 64 + (lane >> 2 & 3) * 16 + 4 * wave + (lane & 3);
+            const int row = gr / b.gx;
+            // this node's place in its plane of the group
+            const int y = lane >> 2 & 3;
+            const int to = (lane >> 4) * 64 + (b.along_y ? 16 * wave + 4 * y : 16 * y + 4 * wave) + (lane & 3);
 #pragma unroll
             for (int c = 0; c < 4; ++c) rows[buf][c][to] = v[c];
             __syncthreads();
 #pragma unroll
             for (int c = 0; c < 4; ++c) v[c] = rows[buf][c][threadIdx.x];
             buf ^= 1;  // the next barrier comes before this half is written again
-            const int X = 16 * gx + (lane & 15), Y = 4 * ty + (lane >> 4), Z = 4 * tz + wave;
-            if (X < b.nx && Y < b.ny && Z < b.nz) {
-                const size_t at = (size_t)X + (size_t)b.nx * ((size_t)Y + (size_t)b.ny * (size_t)Z);
-                if (rho_out) rho_out[at] = v[0];
+            const DenseBox::At d = b.node(gr - row * b.gx, row, lane, wave);
+            if (d.in) {
+                if (rho_out) rho_out[d.at] = v[0];
                 if (u_out) {
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) u_out[c * N + at] = v[1 + c];
+                    for (int c = 0; c < 3; ++c) u_out[c * N + d.at] = v[1 + c];
                 }
             }
         }
@@ -2260,6 +2275,11 @@ static DenseBox dense_box(const Launch &L, int nx, int ny, int nz) {
     b.map = L.tb.map;
     b.tx = (nx + 3) / 4;
     b.ty = (ny + 3) / 4;
+    b.along_y = b.tx == 1;
+    if (b.along_y) {
+        b.tx = b.ty;
+        b.ty = 1;
+    }
     b.gx = (b.tx + 3) / 4;
     b.nx = nx;
     b.ny = ny;
