@@ -466,6 +466,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     c->L.tb.fbase = reinterpret_cast<const uint64_t *>(tb + lay.fld_off);
     c->L.tb.map = reinterpret_cast<const int32_t *>(tb + lay.map_off);
     c->L.off32 = off32;
+    c->L.fill = n > 0 ? (int)(c->n_fluid / n) : 0;
     // The FP64 LBMRT adjoint steps hold 2-3 waves per SIMD (146-240 VGPRs); with
     // one tile per workgroup instead of four they run 4-5% faster with direct
     // stores and with staged ones 1-2% on a 128^3 sphere pack (84.3 against

@@ -2151,6 +2151,35 @@ static bool stage_stores(const Launch &L, const void *dst) {
     return L.n_tiles >= STAGE_MIN_TILES && L.tpw * STAGE_BYTES<S> <= 65536 && reinterpret_cast<uintptr_t>(dst) % 16 == 0;
 }
 
+// LDS bytes a staging workgroup asks for: its stage, and on grids whose tiles
+// are nearly all full (`line` fluid nodes a tile on average) as much as leaves
+// room for `waves` waves per CU alone.  Full tiles in flight on every wave that
+// the registers allow take more than an XCD's 4 MB of L2 between them, and
+// lines that a neighbour is about to read are lost (FP64, 16 waves: 5 MB).  us a
+// step without -> with the limit: 256^3 box, FP64 LBGK 949 -> 908, LBMRT 979 -> 897,
+// FP32 457 -> 451; 384^3, FP64 3302 -> 3034, FP32 1579 -> 1492; 251 x 243 x 197
+// walled, FP64 642 -> 620, FP32 329 -> 326; adjoint step on it, FP64 LBGK 1063 -> 1049,
+// FP32 609 -> 600.
+// The lines: FP64 LBGK gains 2.5% at 61 and 0.4% at 46, LBMRT, whose waves take
+// longer, gains 4-8% at 63 and 64, between -2 and +2% at 62, and loses 1-5% at 60 and
+// 6% at 46; FP32 gains 0.6% at 62 and loses 2-5% at 32.  Tiles from where on, FP64
+// LBGK adjoint step: 8000 +1%, 13824 -0.3%.
+constexpr int FULL_TILES = 61, FULL_TILES_MRT64 = 63, FULL_MIN_TILES = 12288;
+constexpr size_t LDS_OF_CU = 163840, LDS_GRANULE = 1280, LDS_OF_GROUP = 65536;
+template <typename S>
+static size_t stage_request(const Launch &L, int waves, int line) {
+    const size_t stage = (size_t)L.tpw * STAGE_BYTES<S>;
+    if (L.fill < line || L.n_tiles < FULL_MIN_TILES || waves < L.tpw) return stage;
+    const size_t share = LDS_OF_CU / (waves / L.tpw) / LDS_GRANULE * LDS_GRANULE;
+    const size_t ask = share < LDS_OF_GROUP ? share : LDS_OF_GROUP;
+    return ask > stage ? ask : stage;
+}
+// waves per CU of a step (0: FP16 has no limit) and of an adjoint step on full tiles
+template <int ST>
+constexpr int STEP_WAVES_FULL = ST == LBM_F64 ? 12 : ST == LBM_F32 ? 20 : 0;
+template <int ST>
+constexpr int ADJ_WAVES_FULL = ST == LBM_F64 ? 8 : 20;
+
 static dim3 block_of(const Launch &L) { return dim3(64 * L.tpw); }
 
 template <int ST, int MODEL, typename OffT>
@@ -2158,7 +2187,8 @@ static hipError_t step_o(const Launch &L, KArgs a) {
     using S = typename Codec<ST>::S;
     if (a.P.f16_stochastic) a.lw |= STOCHASTIC;
     const bool staged = stage_stores<S>(L, a.dst);
-    const size_t lds = staged ? (size_t)L.tpw * STAGE_BYTES<S> : 0;
+    constexpr int line = ST == LBM_F64 && MODEL >= LBM_MRT_QUASI_COMPRESSIBLE ? FULL_TILES_MRT64 : FULL_TILES;
+    const size_t lds = staged ? stage_request<S>(L, STEP_WAVES_FULL<ST>, line) : 0;
     if (a.P.bc) {
         const auto fn = staged ? k_step_open<ST, MODEL, OffT> : k_step_open_direct<ST, MODEL, OffT>;
         hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), lds, L.stream, KHOT(a), a.P.launch_counter, a.P.bc, a.P);
@@ -2496,7 +2526,9 @@ static hipError_t launch_adj(const Launch &L, const Phys &P, const void *s, cons
     a.out = reinterpret_cast<char *>(out);
     a.grad = grad;
     a.P = P;
-    const size_t lds = staged ? (size_t)L.tpw * (f32 ? STAGE_BYTES<float> : STAGE_BYTES<double>) : 0;
+    const size_t lds = !staged ? 0
+                       : f32   ? stage_request<float>(L, ADJ_WAVES_FULL<LBM_F32>, FULL_TILES)
+                               : stage_request<double>(L, ADJ_WAVES_FULL<LBM_F64>, FULL_TILES);
     hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), lds, L.stream, L.tb.row,
                        reinterpret_cast<const char *>(s), reinterpret_cast<const char *>(eta_in), L.n_tiles,
                        __builtin_ctz((unsigned)L.tpw), L.grid, P.launch_counter, a);

@@ -34,6 +34,7 @@ struct Launch {
     int grid;         // workgroups
     DevTables tb;
     bool off32;       // every lattice byte offset fits in 32 bits
+    int fill;         // fluid nodes of a kept tile on average, rounded down
 };
 
 hipError_t launch_step(const Launch &L, const Phys &P, const void *src, void *dst);
