@@ -2514,12 +2514,21 @@ static AdjFn adj_fn(const Launch &L, bool staged, int model) {
     return nullptr;
 }
 
+// Mean fluid nodes of a tile from which on the FP64 LBMRT adjoint kernels store
+// directly: staged they run 3 waves per SIMD, direct 2, and on full tiles the
+// third costs more in lines lost from the L2 than it covers (us a step, staged
+// and direct: 256^3 box 1570 and 1550, 251 x 243 x 197 walled 1087 and 1072, packs of 60
+// nodes 1370 and 1347, 57 nodes 1239 and 1225, 53 nodes 1096 and 1090, 46 nodes
+// 880 and 887, 40 nodes 665 and 693).
+constexpr int MRT_DIRECT_FILL = 51;
+
 template <template <int, int, typename> class K>
 static hipError_t launch_adj(const Launch &L, const Phys &P, const void *s, const void *eta_in, void *out,
                              double *grad) {
     if (L.n_tiles == 0) return hipSuccess;
     const bool f32 = P.storage == LBM_F32;
-    const bool staged = f32 ? stage_stores<float>(L, out) : stage_stores<double>(L, out);
+    const bool full_mrt = !f32 && P.model >= LBM_MRT_QUASI_COMPRESSIBLE && L.fill >= MRT_DIRECT_FILL;
+    const bool staged = f32 ? stage_stores<float>(L, out) : !full_mrt && stage_stores<double>(L, out);
     const AdjFn fn = f32 ? adj_fn<K, LBM_F32>(L, staged, P.model) : adj_fn<K, LBM_F64>(L, staged, P.model);
     if (!fn) return hipErrorInvalidValue;
     AdjArgs a;

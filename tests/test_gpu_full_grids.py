@@ -57,6 +57,27 @@ c.destroy()
 """)
 
 
+# 24^3 tiles with `nodes` fluid nodes each
+@pytest.mark.parametrize("nodes,storage,model,lds", [(50, 0, 2, 9728), (50, 0, 3, 9728), (51, 0, 2, 0), (64, 0, 3, 0),
+                                                     (51, 0, 0, 38912), (51, 1, 2, 19456)])
+def test_mrt_adjoint_stores_directly(tmp_path, nodes, storage, model, lds):
+    tile = (np.arange(64) >= nodes).astype(np.uint8).reshape(4, 4, 4)
+    np.save(tmp_path / "solid.npy", np.tile(tile, (24, 24, 24)))
+    fake_hip.run(tmp_path, f"""
+import ctypes
+import numpy as np
+c = context(np.load({str(tmp_path / 'solid.npy')!r}), storage={storage}, model={model})
+a, b, g = (ctypes.c_void_p(k << 40) for k in (4, 5, 6))
+hip.notes()
+call("lbm_adjoint_seed", c.ctx, c.state[0], a, g)
+call("lbm_adjoint_step", c.ctx, c.state[0], a, b, g)
+call("lbm_adjoint_final", c.ctx, b, a)
+for n in hip.notes():
+    assert int(n.split()[3]) == {lds} and ("direct" in n) == ({lds} == 0), n
+c.destroy()
+""")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("storage,item", [("f64", 8), ("f32", 4)])
 @pytest.mark.parametrize("model", ["qc", "mrt-qc"])
