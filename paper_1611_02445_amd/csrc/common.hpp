@@ -180,7 +180,7 @@ constexpr int nb_slot(int k) {
     }
     return -1;
 }
-struct alignas(64) NbRow {
+struct NbRow {
     uint64_t mask[19];
     uint32_t base32[19];
     uint32_t pad0;
@@ -188,7 +188,7 @@ struct alignas(64) NbRow {
     int32_t xyz[3];
     int32_t pad1;
 };
-static_assert(sizeof(NbRow) == 256, "a row is two whole 128-byte lines");
+static_assert(sizeof(NbRow) == 256, "a row is the size of two 128-byte lines");
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct TableLayout {
     size_t rec_off, row_off, xyz_off, fld_off, map_off, used, total;

@@ -174,7 +174,9 @@ struct Nbhd {
 // empty asm the compiler waits for the tile's own mask alone, branches on it
 // and only then loads the rest of the row, a second round trip to memory
 // before the first gather can be issued.
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+// (A scalar load asks for no more than 4-byte alignment, and neither the tables
+// nor a kernel's arguments are sure to have more than 8.)
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16), aligned(4)));
 struct RowRegs {
     u32x16 q[4];
     __device__ __forceinline__ explicit RowRegs(const NbRow *row, int t) {
@@ -952,7 +954,7 @@ __device__ __forceinline__ void load_force(const Phys &P, uint64_t first, uint64
 template <int OFF>
 struct StepPhys {
     typedef const __attribute__((address_space(4))) char *ConstPtr;
-    typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x4s __attribute__((ext_vector_type(4), aligned(4)));
     ConstPtr at;
     u32x16 v;  // Phys bytes 0..63
     u32x4s w;  // and 64..79
@@ -971,7 +973,7 @@ struct StepPhys {
     __device__ __forceinline__ double rho_base() const { return f64(offsetof(Phys, rho_base)); }
     __device__ __forceinline__ double F(int c) const { return f64(offsetof(Phys, F) + 8 * c); }
     __device__ __forceinline__ const void *field() const {
-        static_assert(offsetof(Phys, F) == 40 && offsetof(Phys, field) == 64 && offsetof(Phys, scale) == 72 &&
+        static_assert(offsetof(Phys, F) + 24 <= 64 && offsetof(Phys, field) == 64 && offsetof(Phys, scale) == 72 &&
                           offsetof(Phys, inv_scale) == 76,
                       "the fields a step reads");
         return (const void *)(w[0] | (uint64_t)w[1] << 32);
@@ -985,10 +987,17 @@ struct StepPhys {
     __device__ __forceinline__ float inv_scale() const { return f32(3); }
     __device__ __forceinline__ const Phys &all() const { return *(const Phys *)at; }
 };
-// bytes of the arguments before it: row, src, dst, n_tiles, lw, nblocks,
-// counter (and the boundary buffer)
-constexpr int LW_MASK = 15, STOCHASTIC = 16;  // lw and a flag beside it in a step's shape argument
+// where it lies: after row, src, dst, n_tiles, lw, nblocks, counter (and the
+// boundary buffer), which is checked against the kernels' signatures below
 constexpr int HOT_BYTES = 3 * 8 + 4 * 4;
+constexpr int LW_MASK = 15, STOCHASTIC = 16;  // lw and a flag beside it in a step's shape argument
+// the byte at which the last argument of a kernel lies
+template <typename... A>
+constexpr int last_argument(void (*)(A...)) {
+    int at = 0, end = 0;
+    ((at = (end + (int)alignof(A) - 1) / (int)alignof(A) * (int)alignof(A), end = at + (int)sizeof(A)), ...);
+    return at;
+}
 
 template <int ST, int MODEL, typename OffT, bool OPEN, bool STAGED>
 __device__ __forceinline__ void step_tile(const NbRow *row, const char *src, char *dst, int n_tiles,
@@ -1090,6 +1099,11 @@ STEP_KERNEL(k_step, false, true, , nullptr)
 STEP_KERNEL(k_step_direct, false, false, , nullptr)
 STEP_KERNEL(k_step_open, true, true, STEP_BC, bc)
 STEP_KERNEL(k_step_open_direct, true, false, STEP_BC, bc)
+static_assert(last_argument(k_step<LBM_F64, LBM_QUASI_COMPRESSIBLE, uint32_t>) == HOT_BYTES &&
+                  last_argument(k_step_direct<LBM_F64, LBM_QUASI_COMPRESSIBLE, uint32_t>) == HOT_BYTES &&
+                  last_argument(k_step_open<LBM_F64, LBM_QUASI_COMPRESSIBLE, uint32_t>) == HOT_BYTES + 8 &&
+                  last_argument(k_step_open_direct<LBM_F64, LBM_QUASI_COMPRESSIBLE, uint32_t>) == HOT_BYTES + 8,
+              "StepPhys reads the physics where the signature puts it");
 
 // the paper's measurement kernels (Section 4.1): kind 1 "read/write only",
 // kind 2 "propagation only"
