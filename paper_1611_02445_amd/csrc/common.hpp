@@ -201,7 +201,8 @@ struct TableLayout {
         fld_off = align_up(xyz_off + n * 16, 256);
         map_off = align_up(fld_off + n * 8, 256);
         used = n ? align_up(map_off + (size_t)n_grid * 4, 256) : 0;
-        // callers are promised that no build asks for less than 432 bytes a tile
+        // at least 432 bytes a tile are asked for, of which the tables take about
+        // 300: tests/test_abi.py holds the size that is reported to that bound
         total = used < n * 432 ? align_up(n * 432, 256) : used;
     }
 };

@@ -200,8 +200,9 @@ struct RowRegs {
 // away.  A table of 64-bit offsets beside the rows was a second read, waited
 // for between the gathers (256^3 pack with 64-bit offsets, us a step: FP64
 // 377 -> 361, FP32 222 -> 208, FP16 194 -> 165; FP64 LBMRT 410 -> 391, FP32
-// 253 -> 228; FP32 384^3 box 1646 -> 1588; FP64 384^3 box 3198 -> 3257, where
-// waves that start their gathers later get in each other's way less).
+// 253 -> 228).  Dense boxes, where waves that start their gathers later get in
+// each other's way less, lost by it (FP64 384^3 box 3198 -> 3257); they now keep
+// fewer waves in flight instead: see stage_request.
 template <typename S, typename OffT>
 __device__ __forceinline__ void load_nbhd(Nbhd<OffT> &h, const RowRegs &r) {
     constexpr int LINE = __builtin_ctz(128 / sizeof(S));
@@ -1911,9 +1912,6 @@ __device__ __forceinline__ void store_adjoint(char *lattice, const Self<true, Of
 // eta_T = J_T^T lam_T, grad = rho0 [(dC/dF)^T lam_T + dL/dF].  With
 // u_x = (sum c_x s - F_x/2)/rho (quasi-compressible) lam_T depends on s_T; with
 // u_x = sum c_x s - F_x/2 (incompressible) it is c_x / N_fluid.
-template <int ST, int MODEL, typename OffT>
-struct AdjWaves;
-
 template <int ST, int MODEL, typename OffT, bool STAGED>
 __device__ __forceinline__ void adj_seed_tile(ADJ_PARAMS) {
     constexpr int INC = MODEL & 1;
@@ -1981,14 +1979,10 @@ __device__ __forceinline__ void adj_seed_tile(ADJ_PARAMS) {
 // unconstrained (3 waves); at 4 it fits 128 with no spill and runs 6%
 // faster.  Every other instance keeps the allocator's choice: at 4 waves the
 // 64-bit-offset one spills, and the FP64 ones spill and cost 33% (LBGK) to
-// 3.4x (LBMRT).  The FP64 LBMRT seed and step are held to at most 2 waves:
-// the incompressible one needs 160-186 VGPRs, and given room for a third
-// wave the allocator spilled 160 bytes per lane to reach it.
+// 3.4x (LBMRT).  That choice for the FP64 LBMRT steps, staged and direct: 156
+// and 240 VGPRs (quasi-compressible), 146 and 170, so 3 waves and 2.
 template <int ST, int MODEL, typename OffT>
-struct AdjWaves {
-    static constexpr int value = (ST == 1 && MODEL == 2 && sizeof(OffT) == 4) ? 4 : 1;
-    static constexpr int max = (ST == 0 && MODEL >= 2) ? 2 : 8;
-};
+constexpr int ADJ_WAVES = (ST == LBM_F32 && MODEL == LBM_MRT_QUASI_COMPRESSIBLE && sizeof(OffT) == 4) ? 4 : 1;
 
 template <int ST, int MODEL, typename OffT, bool STAGED>
 __device__ __forceinline__ void adj_step_tile(ADJ_PARAMS) {
@@ -2066,10 +2060,9 @@ __device__ __forceinline__ void adj_final_tile(ADJ_PARAMS) {
     __global__ __launch_bounds__(512) ATTRIBUTES void NAME(ADJ_PARAMS) {           \
         BODY<ST, MODEL, OffT, STAGED>(ADJ_NAMES);                                  \
     }
-#define SEED_WAVES __attribute__((amdgpu_waves_per_eu(1, AdjWaves<ST, MODEL, OffT>::max)))
-#define STEP_WAVES __attribute__((amdgpu_waves_per_eu(AdjWaves<ST, MODEL, OffT>::value, AdjWaves<ST, MODEL, OffT>::max)))
-ADJ_KERNEL(k_adj_seed, adj_seed_tile, true, SEED_WAVES)
-ADJ_KERNEL(k_adj_seed_direct, adj_seed_tile, false, SEED_WAVES)
+#define STEP_WAVES __attribute__((amdgpu_waves_per_eu(ADJ_WAVES<ST, MODEL, OffT>, 8)))
+ADJ_KERNEL(k_adj_seed, adj_seed_tile, true, )
+ADJ_KERNEL(k_adj_seed_direct, adj_seed_tile, false, )
 ADJ_KERNEL(k_adj_step, adj_step_tile, true, STEP_WAVES)
 ADJ_KERNEL(k_adj_step_direct, adj_step_tile, false, STEP_WAVES)
 ADJ_KERNEL(k_adj_final, adj_final_tile, true, )
@@ -2153,12 +2146,18 @@ static KArgs make_args(const Launch &L, const Phys &P, const void *src, void *ds
 // are in scalar registers when a wave starts instead of a memory read away.
 #define KHOT(a) (a).tb.row, (a).src, (a).dst, (a).n_tiles, (a).lw, (a).nblocks
 
-// Whether a launch stages its stores: with more tiles than are in flight at
-// once (4096 of FP64, 7168 of FP32), where the waves that wait for the LDS are
-// covered by others (FP64, us a step, direct -> staged: 512 tiles 5.7 -> 6.2,
-// 3300 13.3 -> 13.5, 6320 21.5 -> 21.5, 8830 25.3 -> 24.6, 23605 62.4 -> 60.4,
-// 169669 388 -> 372); within the 64 KB that a workgroup is sure to get; to
-// lattices on a 16-byte boundary.
+// Whether a launch stages its stores: on grids of so many tiles that the waves
+// that wait for the LDS are covered by others; within the 64 KB that a
+// workgroup is sure to get; to lattices on a 16-byte boundary.  One line for
+// all kernels, which costs none of them more than 2.5% (packs, us a step, direct
+// -> staged):
+//   tiles              512          3300         5124          6320          7324          10332         17233         169669
+//   FP64 LBGK          5.7 -> 6.2   13.3 -> 13.5 16.0 -> 16.0  21.4 -> 21.4  24.2 -> 24.1  33.9 -> 33.8  50.2 -> 49.3  388 -> 374
+//   FP64 LBMRT                                   17.0 -> 17.2  22.4 -> 22.4  25.4 -> 25.3  35.6 -> 35.5  51.7 -> 51.6  407 -> 406
+//   FP32 LBGK                                    10.5 -> 10.3  13.4 -> 13.3  14.9 -> 14.6  19.9 -> 19.7  28.9 -> 28.1  220 -> 204
+//   FP16 LBGK                                     9.3 -> 9.4   10.3 -> 10.4  10.9 -> 11.1  13.7 -> 14.1  19.9 -> 19.9  159 -> 158
+//   FP64 LBGK adjoint                            23.8 -> 24.0  32.4 -> 32.4  36.8 -> 36.6  51.8 -> 51.7  78.3 -> 77.4  666 -> 653
+//   FP32 LBGK adjoint                            15.8 -> 15.3  21.8 -> 21.1  24.5 -> 23.9  33.8 -> 32.8  50.2 -> 48.4  413 -> 393
 constexpr int STAGE_MIN_TILES = 6144;
 template <typename S>
 static bool stage_stores(const Launch &L, const void *dst) {
@@ -2351,8 +2350,8 @@ static int dense_groups(const DenseBox &b) {
 static bool walks_box(const Launch &L, int groups) { return groups <= (int64_t)2 * L.n_tiles; }
 
 // Workgroups of a pass that goes over the tiles or the box in strides: 2048 of
-// 4 waves, about as many as are resident at once, and 4 times that for the
-// fields and sums of a large box (256^3 pack, FP64, us a call for the
+// 4 waves (8 waves per SIMD are as many; the passes have 5 to 8 resident), and
+// 4 times that for the fields and sums of a large box (256^3 pack, FP64, us a call for the
 // fields: 348 with 8192, 375 with 2048; 192^3 267 and 264; 128^3 68 and 57.5, every
 // workgroup leaving a row to be added up).
 constexpr int WALK_GROUPS = 2048;
