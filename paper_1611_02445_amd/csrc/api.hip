@@ -321,7 +321,7 @@ extern "C" int lbm_required_bytes(const lbm_tiles *tiles, const lbm_params *para
     if (!out) return fail(LBM_E_INVAL, "NULL output");
     const size_t n = (size_t)tiles->n_tiles;
     out->state_bytes = lattice_elems(tiles, params->storage) * storage_size(params->storage);
-    out->table_bytes = TableLayout((int64_t)n, grid_tiles(tiles->nx, tiles->ny, tiles->nz)).total;
+    out->table_bytes = TableLayout((int64_t)n, tiles->nx, tiles->ny, tiles->nz).total;
     out->scratch_bytes = (n + 1) * NSUM * sizeof(double);
     const size_t fe = field_entries(tiles);
     out->force_bytes = fe * arith_size(params->storage);
@@ -397,7 +397,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     // get 128-byte lines, where every tile's data begins
     const bool off32 = c->state_bytes <= (size_t)UINT32_MAX && !c->params.wide_offsets;
     const uint64_t line = 128 / storage_size(params->storage);
-    const TableLayout lay(n, grid_tiles(tiles->nx, tiles->ny, tiles->nz));
+    const TableLayout lay(n, tiles->nx, tiles->ny, tiles->nz);
     if (n > 0) try {
         // device tile d holds discovery tile perm[d]; neighbour numbers are
         // translated with the inverse permutation
@@ -413,7 +413,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
         uint64_t *fbase = reinterpret_cast<uint64_t *>(host.data() + lay.fld_off);
         int32_t *map = reinterpret_cast<int32_t *>(host.data() + lay.map_off);
         const int64_t gtx = ((int64_t)c->nx + 3) / 4, gty = ((int64_t)c->ny + 3) / 4;
-        std::fill(map, map + grid_tiles(c->nx, c->ny, c->nz), -1);
+        std::fill(map, map + lay.map_size, -1);
         uint64_t next = 0, next_field = 0;
         for (int64_t d = 0; d < n; ++d) {
             const int64_t i = perm[d];
@@ -429,7 +429,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
             for (int a = 0; a < 3; ++a) xyz[4 * d + a] = tiles->tile_xyz[3 * i + a];
             for (int a = 0; a < 3; ++a) c->corner[3 * d + a] = tiles->tile_xyz[3 * i + a];
             xyz[4 * d + 3] = 0;
-            map[xyz[4 * d] / 4 + gtx * (xyz[4 * d + 1] / 4 + gty * (int64_t)(xyz[4 * d + 2] / 4))] = (int32_t)d;
+            if (lay.map_size) map[xyz[4 * d] / 4 + gtx * (xyz[4 * d + 1] / 4 + gty * (int64_t)(xyz[4 * d + 2] / 4))] = (int32_t)d;
         }
         // neighbourhood rows (needs every tile's record first)
         for (int64_t d = 0; d < n; ++d) {
@@ -466,6 +466,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     c->L.tb.fbase = reinterpret_cast<const uint64_t *>(tb + lay.fld_off);
     c->L.tb.map = reinterpret_cast<const int32_t *>(tb + lay.map_off);
     c->L.off32 = off32;
+    c->L.walk = lay.map_size > 0;
     c->L.fill = n > 0 ? (int)(c->n_fluid / n) : 0;
     // The FP64 LBMRT adjoint steps hold 2-3 waves per SIMD (146-240 VGPRs); with
     // one tile per workgroup instead of four they run 4-5% faster with direct

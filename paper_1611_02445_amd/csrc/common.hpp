@@ -154,7 +154,8 @@ inline uint64_t run_elems(uint64_t mask, int storage) {
 //   [xyz_off]    int32  [n_tiles][4]: corner x, y, z, 0
 //   [fld_off]    uint64 [n_tiles]: entry offset of the tile's per-node field run
 //   [map_off]    int32  [tz][ty][tx]: device tile number of each tile of the
-//                box, -1 for a dropped one (kernels that walk a dense array)
+//                box, -1 for a dropped one (kernels that walk a dense array;
+//                absent where they do not)
 // The neighbourhood is gathered once on the host, so a wave reads it with a
 // few wide scalar loads instead of chasing 19 tile numbers.  Everything a step
 // needs to know about a tile is in its row: one round trip to memory, where a
@@ -190,17 +191,39 @@ struct NbRow {
 };
 static_assert(sizeof(NbRow) == 256, "a row is the size of two 128-byte lines");
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+// Groups of 4 tiles along x (along y in a box of one tile along x) in which a
+// dense array is walked, -1 if there are too many to number.
+inline int64_t dense_groups(int32_t nx, int32_t ny, int32_t nz) {
+    const int64_t tx = ((int64_t)nx + 3) / 4, ty = ((int64_t)ny + 3) / 4, tz = ((int64_t)nz + 3) / 4;
+    const int64_t row = tx == 1 ? (ty + 3) / 4 : (tx + 3) / 4, rows = tx == 1 ? tz : ty * tz;
+    return row > 0 && rows > (int64_t)(INT32_MAX / 2) / row ? -1 : row * rows;
+}
+// Whether a pass over a dense array walks the box, or takes its kept tiles one
+// by one after the array has been cleared: it walks up to two groups of four
+// tiles per kept tile.  A 384^3 box, FP64, us walked and tile by tile:
+//   kept tiles (groups per kept tile)  all fields  sums alone   lattice    per-node field
+//   one 170 x 170 duct (1.2)            755   864   313   290  2271  2415   390   378
+//   15% scattered (1.7)                 668   983   251   226  2780  3338   475   560
+//   10% scattered (2.5)                 582   787   178   157  2635  2790   446   473
+//   one 120 x 120 duct (2.6)            582   601   179   154  2040  1975   355   309
+//   6% scattered (4.2)                  516   624   138   102  2305  2327   413   401
+//   one 64 x 64 duct (9)                456   421   119    53  1907  1663   341   259
+inline bool walks_box(int64_t n_tiles, int32_t nx, int32_t ny, int32_t nz) {
+    const int64_t groups = dense_groups(nx, ny, nz);
+    return n_tiles > 0 && groups >= 0 && groups <= 2 * n_tiles;
+}
 struct TableLayout {
-    size_t rec_off, row_off, xyz_off, fld_off, map_off, used, total;
-    // n_grid: tiles of the whole box, kept or not
-    TableLayout(int64_t n_tiles, int64_t n_grid) {
+    size_t rec_off, row_off, xyz_off, fld_off, map_off, map_size, used, total;
+    // the map is there if the box is walked
+    TableLayout(int64_t n_tiles, int32_t nx, int32_t ny, int32_t nz) {
         const size_t n = (size_t)n_tiles;
         rec_off = 0;
         row_off = align_up(rec_off + n * sizeof(TileRec), 256);
         xyz_off = align_up(row_off + n * sizeof(NbRow), 256);
         fld_off = align_up(xyz_off + n * 16, 256);
         map_off = align_up(fld_off + n * 8, 256);
-        used = n ? align_up(map_off + (size_t)n_grid * 4, 256) : 0;
+        map_size = walks_box(n_tiles, nx, ny, nz) ? ((size_t)nx + 3) / 4 * (((size_t)ny + 3) / 4) * (((size_t)nz + 3) / 4) : 0;
+        used = n ? align_up(map_off + map_size * 4, 256) : 0;
         // at least 432 bytes a tile are asked for, of which the tables take about
         // 300: tests/test_abi.py holds the size that is reported to that bound
         total = used < n * 432 ? align_up(n * 432, 256) : used;
@@ -214,10 +237,6 @@ struct DevTables {
     const uint64_t *fbase;
     const int32_t *map;
 };
-inline int64_t grid_tiles(int32_t nx, int32_t ny, int32_t nz) {
-    return (((int64_t)nx + 3) / 4) * (((int64_t)ny + 3) / 4) * (((int64_t)nz + 3) / 4);
-}
-
 // reduction scratch: rows of 8 doubles, at most one row per tile + the final 8
 constexpr int NSUM = 8;
 

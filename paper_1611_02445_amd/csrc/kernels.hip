@@ -2330,25 +2330,6 @@ static DenseBox dense_box(const Launch &L, int nx, int ny, int nz) {
     return b;
 }
 
-// workgroups of a dense walk, or -1 when they do not fit a grid (no such box
-// fits the memory)
-static int dense_groups(const DenseBox &b) {
-    const int64_t g = (int64_t)b.gx * b.ty * ((b.nz + 3) / 4);
-    return g <= INT32_MAX ? (int)g : -1;
-}
-
-// Whether a pass over a dense array walks the box, or takes its kept tiles one
-// by one after the array has been cleared: it walks up to two groups of four
-// tiles per kept tile.  A 384^3 box, FP64, us walked and tile by tile:
-//   kept tiles (groups per kept tile)  all fields  sums alone   lattice    per-node field
-//   one 170 x 170 duct (1.2)            755   864   313   290  2271  2415   390   378
-//   15% scattered (1.7)                 668   983   251   226  2780  3338   475   560
-//   10% scattered (2.5)                 582   787   178   157  2635  2790   446   473
-//   one 120 x 120 duct (2.6)            582   601   179   154  2040  1975   355   309
-//   6% scattered (4.2)                  516   624   138   102  2305  2327   413   401
-//   one 64 x 64 duct (9)                456   421   119    53  1907  1663   341   259
-static bool walks_box(const Launch &L, int groups) { return groups <= (int64_t)2 * L.n_tiles; }
-
 // Workgroups of a pass that goes over the tiles or the box in strides: 2048 of
 // 4 waves (8 waves per SIMD are as many; the passes have 5 to 8 resident), and
 // 4 times that for the fields and sums of a large box (256^3 pack, FP64, us a call for the
@@ -2364,10 +2345,9 @@ constexpr int MACRO_GROUPS = 8192;
 template <int ST>
 static hipError_t macro_t(const Launch &L, const KArgs &a, double *rho, double *u, int nx, int ny, int nz,
                           double *partials, int *rows) {
-    const DenseBox b = dense_box(L, nx, ny, nz);
-    const int groups = dense_groups(b);
-    if (groups < 0) return hipErrorInvalidValue;
-    if (walks_box(L, groups)) {
+    if (L.walk) {
+        const DenseBox b = dense_box(L, nx, ny, nz);
+        const int groups = (int)dense_groups(nx, ny, nz);
         int grid = groups < 4 * MACRO_GROUPS ? WALK_GROUPS : MACRO_GROUPS;
         if (grid > groups) grid = groups;
         if (grid > L.n_tiles) grid = L.n_tiles;
@@ -2412,10 +2392,9 @@ template <class K, class... Args>
 static hipError_t to_dense(const Launch &L, K by_box, K by_tile, const KArgs &a, int nx, int ny, int nz,
                            size_t out_elems, double *out, Args... args) {
     const DenseBox b = dense_box(L, nx, ny, nz);
-    const int groups = dense_groups(b);
-    if (groups < 0) return hipErrorInvalidValue;
     const int threads = 64 << WALK_LW;
-    if (walks_box(L, groups)) {
+    if (L.walk) {
+        const int groups = (int)dense_groups(nx, ny, nz);
         hipLaunchKernelGGL(by_box, dim3(groups < WALK_GROUPS ? groups : WALK_GROUPS), dim3(threads), 0, L.stream, a, b,
                            groups, args...);
         return hipGetLastError();

@@ -34,6 +34,7 @@ struct Launch {
     int grid;         // workgroups
     DevTables tb;
     bool off32;       // every lattice byte offset fits in 32 bits
+    bool walk;        // passes over a dense array walk the box (tb.map is there)
     int fill;         // fluid nodes of a kept tile on average, rounded down
 };
 
