@@ -398,6 +398,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     const bool off32 = c->state_bytes <= (size_t)UINT32_MAX && !c->params.wide_offsets;
     const uint64_t line = 128 / storage_size(params->storage);
     const TableLayout lay(n, tiles->nx, tiles->ny, tiles->nz);
+    bool walk = lay.map_size > 0;
     if (n > 0) try {
         // device tile d holds discovery tile perm[d]; neighbour numbers are
         // translated with the inverse permutation
@@ -429,7 +430,11 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
             for (int a = 0; a < 3; ++a) xyz[4 * d + a] = tiles->tile_xyz[3 * i + a];
             for (int a = 0; a < 3; ++a) c->corner[3 * d + a] = tiles->tile_xyz[3 * i + a];
             xyz[4 * d + 3] = 0;
-            if (lay.map_size) map[xyz[4 * d] / 4 + gtx * (xyz[4 * d + 1] / 4 + gty * (int64_t)(xyz[4 * d + 2] / 4))] = (int32_t)d;
+            if (lay.map_size) {
+                int32_t &at = map[xyz[4 * d] / 4 + gtx * (xyz[4 * d + 1] / 4 + gty * (int64_t)(xyz[4 * d + 2] / 4))];
+                walk &= at < 0;  // a tiling of the caller's own may have two tiles at one place
+                at = (int32_t)d;
+            }
         }
         // neighbourhood rows (needs every tile's record first)
         for (int64_t d = 0; d < n; ++d) {
@@ -466,7 +471,7 @@ extern "C" int lbm_create(const lbm_tiles *tiles, const lbm_params *params, void
     c->L.tb.fbase = reinterpret_cast<const uint64_t *>(tb + lay.fld_off);
     c->L.tb.map = reinterpret_cast<const int32_t *>(tb + lay.map_off);
     c->L.off32 = off32;
-    c->L.walk = lay.map_size > 0;
+    c->L.walk = walk;
     c->L.fill = n > 0 ? (int)(c->n_fluid / n) : 0;
     // The FP64 LBMRT adjoint steps hold 2-3 waves per SIMD (146-240 VGPRs); with
     // one tile per workgroup instead of four they run 4-5% faster with direct

@@ -42,3 +42,17 @@ for n in (1 << 12, 1 << 16, 1 << 23, 0x7ffffffc):
     assert [x.split()[0][:20] for x in n[:2]] == [n[0].split()[0][:20]] * 2 and "k_sums" in n[2], n
     call("lbm_destroy", ctx)
 """)
+
+
+def test_two_tiles_at_one_place(tmp_path):
+    """Every tile of the caller's tiling counts in the sums: the tiles are taken one by one."""
+    fake_hip.run(tmp_path, HEAD + """
+for corners, kernel in (([(0, 0, 0), (4, 0, 0), (4, 4, 4)], "k_fields"), ([(0, 0, 0), (4, 0, 0), (4, 0, 0)], "k_sums")):
+    ctx, size, mem = create(tiling(8, corners))
+    hip.notes()
+    s = (ctypes.c_double * 8)()
+    call("lbm_macroscopic", ctx, None, None, s)
+    n = hip.notes()
+    assert kernel in n[0], n
+    call("lbm_destroy", ctx)
+""")
