@@ -2245,8 +2245,8 @@ static hipError_t calib_o(const Launch &L, const KArgs &a) {
     using S = typename C::S;
     const bool staged = stage_stores<S>(L, a.dst);
     const auto fn = staged ? k_calib<S, C::RUNS, KIND, OffT, true> : k_calib<S, C::RUNS, KIND, OffT, false>;
-    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), staged ? (size_t)L.tpw * STAGE_BYTES<S> : 0, L.stream, KHOT(a),
-                       a.tb.rec);
+    const size_t lds = staged ? stage_request<S>(L, STEP_WAVES_FULL<ST>, FULL_TILES) : 0;  // as an LBGK step's
+    hipLaunchKernelGGL(fn, dim3(L.grid), block_of(L), lds, L.stream, KHOT(a), a.tb.rec);
     return hipGetLastError();
 }
 

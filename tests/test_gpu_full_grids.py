@@ -51,6 +51,8 @@ def lds(*args):
     (n,) = hip.notes()
     return int(n.split()[3])
 assert lds("lbm_step", c.ctx, 1) == {step}
+if {model} == 0:  # the measurement kernels take the shape of an LBGK step
+    assert lds("lbm_calib_step", c.ctx, 1, a, b) == lds("lbm_calib_step", c.ctx, 2, a, b) == {step}
 if {adjoint} is not None:
     assert lds("lbm_adjoint_step", c.ctx, c.state[0], a, b, g) == {adjoint}
 c.destroy()
